@@ -397,13 +397,13 @@ static std::vector<int> order_desc_stable(const std::vector<uint64_t>& key) {
 
 // dense near-field blocks of every slot: far-tier entries, then self/near-tier ones
 template <typename T, bool DLP>
-static void launch_near(gcq_context* ctx, dim3 g1, dim3 g2, int nnear, const double2* sig, int nslot,
+static void launch_near(gcq_context* ctx, dim3 g1, dim3 g2, int nnear, const double2* sig, int nslot, double smax,
                         cpx<T>* out, int64_t stride) {
   hipLaunchKernelGGL((near_far_tier<T, DLP>), g1, dim3(256), 0, ctx->stream, ctx->tab(), ctx->d_blk.as<int>(),
                      ctx->d_near_ids.as<int>(), ctx->d_near_off.as<int64_t>(), 0, nnear, int64_t(0), sig, nslot,
-                     out, stride);
+                     smax, out, stride);
   hipLaunchKernelGGL((near_sing<T, DLP>), g2, dim3(256), 0, ctx->stream, ctx->tab(), ctx->d_sing.as<SingEntry>(),
-                     int64_t(0), ctx->n_sing, int64_t(0), sig, nslot, out, stride);
+                     int64_t(0), ctx->n_sing, int64_t(0), sig, nslot, smax, out, stride);
 }
 
 int rank_predict_device(gcq_context* ctx, const float* d_x, int m, float* d_out);
@@ -461,11 +461,13 @@ GCQ_API int gcq_aca_blocks(gcq_context* ctx, const int32_t* freq_idx, int32_t n_
     GCQ_TRY(H.near.ensure(size_t(acc_near) * nslot * esz0 + 256));
   }
   GCQ_TRY(upload(H.d_near_off, H.near_off, ctx->stream));
+  double smax = 0.0;
   {
     std::vector<double2> sg(nslot);
     for (int q = 0; q < nslot; ++q) {
       std::complex<double> v = ctx->s[fr[q]] / ctx->c;
       sg[q] = make_double2(v.real(), v.imag());
+      smax = std::max(smax, std::abs(v));
     }
     GCQ_TRY(upload(H.d_sig, sg, ctx->stream));
   }
@@ -480,17 +482,17 @@ GCQ_API int gcq_aca_blocks(gcq_context* ctx, const int32_t* freq_idx, int32_t n_
   GCQ_HIP(hipEventCreate(&en.b));
   GCQ_HIP(hipEventRecord(en.a, ctx->stream));
   if (nnear > 0) {
-    const dim3 g1(std::min(nnear, 65536)), g2(4096);
+    const dim3 g1(std::min(nnear, 65536), NEAR_SPLIT), g2(4096);
     if (precision == GCQ_C128) {
       if (H.dlp)
-        launch_near<double, true>(ctx, g1, g2, nnear, H.d_sig.as<double2>(), nslot, H.near.as<cpx<double>>(), acc_near);
+        launch_near<double, true>(ctx, g1, g2, nnear, H.d_sig.as<double2>(), nslot, smax, H.near.as<cpx<double>>(), acc_near);
       else
-        launch_near<double, false>(ctx, g1, g2, nnear, H.d_sig.as<double2>(), nslot, H.near.as<cpx<double>>(), acc_near);
+        launch_near<double, false>(ctx, g1, g2, nnear, H.d_sig.as<double2>(), nslot, smax, H.near.as<cpx<double>>(), acc_near);
     } else {
       if (H.dlp)
-        launch_near<float, true>(ctx, g1, g2, nnear, H.d_sig.as<double2>(), nslot, H.near.as<cpx<float>>(), acc_near);
+        launch_near<float, true>(ctx, g1, g2, nnear, H.d_sig.as<double2>(), nslot, smax, H.near.as<cpx<float>>(), acc_near);
       else
-        launch_near<float, false>(ctx, g1, g2, nnear, H.d_sig.as<double2>(), nslot, H.near.as<cpx<float>>(), acc_near);
+        launch_near<float, false>(ctx, g1, g2, nnear, H.d_sig.as<double2>(), nslot, smax, H.near.as<cpx<float>>(), acc_near);
     }
   }
   GCQ_HIP(hipGetLastError());

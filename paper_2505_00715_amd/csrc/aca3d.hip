@@ -769,12 +769,12 @@ static void launch_far(bool dlp, int nw, int grid, hipStream_t st, Args... args)
 // dense near-field tensor of the blocks [q0, q1): far-tier entries, then self/near-tier ones
 template <typename T, bool DLP>
 static void launch_near3(gcq_context* ctx, dim3 g1, dim3 g2, int q0, int q1, int64_t base0, int64_t s0,
-                         int64_t s1, int nK, cpx<T>* out, int64_t span) {
+                         int64_t s1, int nK, double smax, cpx<T>* out, int64_t span) {
   hipLaunchKernelGGL((near_far_tier<T, DLP>), g1, dim3(256), 0, ctx->stream, ctx->tab(), ctx->d_blk.as<int>(),
                      ctx->d_near_ids.as<int>(), ctx->d_near_off.as<int64_t>(), q0, q1, base0,
-                     ctx->scratchC.as<double2>(), nK, out, span);
+                     ctx->scratchC.as<double2>(), nK, smax, out, span);
   hipLaunchKernelGGL((near_sing<T, DLP>), g2, dim3(256), 0, ctx->stream, ctx->tab(), ctx->d_sing.as<SingEntry>(),
-                     s0, s1, base0, ctx->scratchC.as<double2>(), nK, out, span);
+                     s0, s1, base0, ctx->scratchC.as<double2>(), nK, smax, out, span);
 }
 
 // side streams and fork/join events of the context, created on first use
@@ -868,9 +868,11 @@ int aca3d_run(gcq_context* ctx, double tol_aca, double tol, int32_t max_freq_ran
     return cost(a) > cost(b);
   });
   std::vector<double2> sig(nK);
+  double smax = 0.0;
   for (int p = 0; p < nK; ++p) {
     std::complex<double> s = ctx->s[ctx->K[p]] / ctx->c;
     sig[p] = make_double2(s.real(), s.imag());
+    smax = std::max(smax, std::abs(s));
   }
   const int aca_cap = 64;
   const int64_t csz = csize(precision);
@@ -1047,17 +1049,17 @@ int aca3d_run(gcq_context* ctx, double tol_aca, double tol, int32_t max_freq_ran
         const int64_t s0 = int64_t(std::lower_bound(sing_off.begin(), sing_off.end(), base0) - sing_off.begin());
         const int64_t s1 = int64_t(std::lower_bound(sing_off.begin(), sing_off.end(), base0 + span) - sing_off.begin());
         GCQ_TRY(timed_begin(ctx));
-        const dim3 g1(std::min(q1 - q0, 65536)), g2(4096);
+        const dim3 g1(std::min(q1 - q0, 65536), NEAR_SPLIT), g2(4096);
         if (precision == GCQ_C128) {
           if (dlp)
-            launch_near3<double, true>(ctx, g1, g2, q0, q1, base0, s0, s1, nK, tensor.as<cpx<double>>(), span);
+            launch_near3<double, true>(ctx, g1, g2, q0, q1, base0, s0, s1, nK, smax, tensor.as<cpx<double>>(), span);
           else
-            launch_near3<double, false>(ctx, g1, g2, q0, q1, base0, s0, s1, nK, tensor.as<cpx<double>>(), span);
+            launch_near3<double, false>(ctx, g1, g2, q0, q1, base0, s0, s1, nK, smax, tensor.as<cpx<double>>(), span);
         } else {
           if (dlp)
-            launch_near3<float, true>(ctx, g1, g2, q0, q1, base0, s0, s1, nK, tensor.as<cpx<float>>(), span);
+            launch_near3<float, true>(ctx, g1, g2, q0, q1, base0, s0, s1, nK, smax, tensor.as<cpx<float>>(), span);
           else
-            launch_near3<float, false>(ctx, g1, g2, q0, q1, base0, s0, s1, nK, tensor.as<cpx<float>>(), span);
+            launch_near3<float, false>(ctx, g1, g2, q0, q1, base0, s0, s1, nK, smax, tensor.as<cpx<float>>(), span);
         }
         GCQ_HIP(hipGetLastError());
         ms_tensor += timed_end(ctx, "aca3d_tensor_batch");

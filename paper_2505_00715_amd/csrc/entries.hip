@@ -1,8 +1,11 @@
 // Dense entries V(s_f)[rows[a], cols[b]] (single layer) and K(s_f)[rows[a],
 // cols[b]] (double layer) for index and frequency lists.
+#include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 #include "internal.h"
+#include "series.h"
 
 namespace gcq {
 
@@ -39,21 +42,57 @@ static void* scratch_ptr(int device) {
   return (device >= 0 && device < NOALLOC_MAX_DEVICES) ? g_scratch_ptr[device] : nullptr;
 }
 
-// one thread per (a, b); the frequencies loop inside so that the geometry of
-// the pair is loaded once.  out[(f * ncol + b) * nrow + a].
-template <typename T, bool DLP>
-__global__ void __launch_bounds__(256) assemble_kernel(Tab tab, const int* __restrict__ prow,
+// TILE pairs (a, b) a workgroup of four waves; out[(f * ncol + b) * nrow + a].
+// Far pairs, a thread each, evaluate their frequencies from distances computed
+// once: in float from SERIES_MIN_F frequencies on by the series of series.h (one
+// exponential and a short polynomial per frequency), below that as single
+// entries in float.  Self and near-tier pairs go to a list in LDS, and the
+// waves then take one each, their points spread over the lanes: left to their
+// own lanes they held the other 63 up for 112 serial float64 points per
+// frequency (2048 x 2048 entries of a 20k-triangle housing at 17 frequencies,
+// complex64: 9.2 ms, now 0.47).
+// TILE = 256: a thread holds one pair and all its frequencies.  TILE = 64: the
+// four waves hold the same 64 pairs and share their frequencies and near
+// pairs, for requests of less than ASSEMBLE_SMALL pairs, which would leave
+// compute units idle and are bound by one workgroup's latency (64 x 320 entries
+// of a sphere at 3 frequencies, complex128: 523 us with a thread per pair and
+// no list, 60 with TILE = 256, now 26).
+constexpr int64_t ASSEMBLE_SMALL = 1 << 16;
+template <typename T, bool DLP, int TILE>
+__global__ void __launch_bounds__(FAR_THREADS) assemble_kernel(Tab tab, const int* __restrict__ prow,
                                                        const int* __restrict__ pcol, int64_t nrow,
                                                        int64_t ncol, const double2* __restrict__ sig,
-                                                       int nf, cpx<T>* __restrict__ out) {
-  const int64_t id = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (id >= nrow * ncol) return;
-  const int64_t a = id % nrow, b = id / nrow;
-  const int pi = prow[a], pj = pcol[b];
-  for (int f = 0; f < nf; ++f) {
-    double2 s = sig[f];
-    out[(int64_t(f) * ncol + b) * nrow + a] =
-        DLP ? dlp_entry_part<T>(tab, pi, pj, s.x, s.y, false, 0, 1) : entry<T>(tab, pi, pj, s.x, s.y, false);
+                                                       int nf, double smax, cpx<T>* __restrict__ out) {
+  __shared__ double lds[4 * SERIES_LDS], pts[far_pts<T>()];
+  __shared__ int list[TILE], cnt;
+  const int w = uni(threadIdx.x / WAVE);
+  const int k0 = TILE == 64 ? w : 0, kstep = TILE == 64 ? 4 : 1;
+  const int64_t total = nrow * ncol, id = int64_t(blockIdx.x) * TILE + threadIdx.x % TILE;
+  const int64_t ic = id < total ? id : total - 1;
+  const int64_t b = total <= 0x7fffffff ? int(ic) / int(nrow) : ic / nrow;
+  const int pi = prow[ic - b * nrow], pj = pcol[b];
+  if (threadIdx.x == 0) cnt = 0;
+  __syncthreads();
+  const bool far = pi != pj && !is_near(tab, pi, pj);
+  if (!far && id < total && threadIdx.x < TILE) list[atomicAdd(&cnt, 1)] = threadIdx.x;
+  cpx<T>* o = out + id;
+  if (sizeof(T) == 8 || nf >= SERIES_MIN_F) {
+    far_pair<T, DLP>(tab, pi, pj, far && id < total, sig, k0, nf, kstep, smax,
+                     sizeof(T) == 4 ? pts + threadIdx.x : pts, [&](int f, cpx<T> v) { o[int64_t(f) * total] = v; });
+  } else if (far && id < total) {
+    for (int f = k0; f < nf; f += kstep) {
+      const double2 s = sig[f];
+      o[int64_t(f) * total] = op_entry_part<T, true, DLP>(tab, pi, pj, s.x, s.y, true, 0, 1);
+    }
+  }
+  __syncthreads();
+  const int n = uni(cnt);
+  for (int q = w; q < n; q += 4) {
+    const int64_t e = int64_t(blockIdx.x) * TILE + uni(list[q]);
+    const int64_t eb = e / nrow;
+    cpx<T>* oe = out + e;
+    near_pair<T, DLP>(tab, uni(prow[e - eb * nrow]), uni(pcol[eb]), sig, nf, smax, lds + w * SERIES_LDS,
+                      [&](int f, cpx<T> v) { oe[int64_t(f) * total] = v; });
   }
 }
 
@@ -84,14 +123,17 @@ static int assemble(gcq_context* ctx, const int32_t* rows, int64_t n_rows, const
     pc[b] = ctx->iperm[cols[b]];
   }
   std::vector<double2> sig(n_fidx);
+  double smax = 0.0;
   for (int f = 0; f < n_fidx; ++f) {
     if (freq_idx[f] < 0 || freq_idx[f] >= ctx->L)
       return fail(GCQ_ERR_ARG, "frequency index out of range");
     std::complex<double> sg = ctx->s[freq_idx[f]] / ctx->c;
     sig[f] = make_double2(sg.real(), sg.imag());
+    smax = std::max(smax, std::abs(sg));
   }
   const int64_t total = n_rows * n_cols;
-  const int64_t nblk = (total + 255) / 256;
+  const int tile = total < ASSEMBLE_SMALL ? 64 : 256;
+  const int64_t nblk = (total + tile - 1) / tile;
   if (nblk > 0x7fffffff) return fail(GCQ_ERR_ARG, "request too large");
   const int* d_rows;
   const int* d_cols;
@@ -121,14 +163,22 @@ static int assemble(gcq_context* ctx, const int32_t* rows, int64_t n_rows, const
     d_sig = ctx->scratchC.as<double2>();
     GCQ_TRY(timed_begin(ctx));
   }
+  auto go = [&](auto zero, auto t) {
+    using T = decltype(zero);
+    hipLaunchKernelGGL((assemble_kernel<T, DLP, decltype(t)::value>), dim3(unsigned(nblk)), dim3(FAR_THREADS), 0,
+                       ctx->stream, ctx->tab(), d_rows, d_cols, n_rows, n_cols, d_sig, n_fidx, smax,
+                       reinterpret_cast<cpx<T>*>(out_dev));
+  };
+  auto sized = [&](auto zero) {
+    if (tile == 64)
+      go(zero, std::integral_constant<int, 64>());
+    else
+      go(zero, std::integral_constant<int, 256>());
+  };
   if (precision == GCQ_C128)
-    hipLaunchKernelGGL((assemble_kernel<double, DLP>), dim3(unsigned(nblk)), dim3(256), 0, ctx->stream,
-                       ctx->tab(), d_rows, d_cols, n_rows, n_cols, d_sig, n_fidx,
-                       reinterpret_cast<cpx<double>*>(out_dev));
+    sized(double());
   else
-    hipLaunchKernelGGL((assemble_kernel<float, DLP>), dim3(unsigned(nblk)), dim3(256), 0, ctx->stream,
-                       ctx->tab(), d_rows, d_cols, n_rows, n_cols, d_sig, n_fidx,
-                       reinterpret_cast<cpx<float>*>(out_dev));
+    sized(float());
   GCQ_HIP(hipGetLastError());
   if (!staged) timed_end(ctx, DLP ? "assemble_dlp" : "assemble");
   return GCQ_OK;
