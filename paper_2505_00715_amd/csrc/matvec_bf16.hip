@@ -22,7 +22,7 @@
 // Y_I += sum_d f_d o (D_d X_J).  Work items are rows of one row cluster with all
 // its far (or all its near) blocks; a workgroup's waves own the frequency
 // columns, accumulate the item's rows in registers and store them once into
-// the level buffer of the cluster's depth (near blocks: the level after the
+// the level buffer of the cluster's depth (near blocks: a level after the
 // deepest); a last pass sums the levels of each row into Y.  No atomics.
 #include <algorithm>
 #include <cstring>
@@ -171,6 +171,8 @@ constexpr int BF_MC = 64;    // rows of a work item: BF_RT 32-row tiles
 constexpr int BF_RT = BF_MC / 32;
 constexpr int BF_NX = 8;     // work lists of the product, one per XCD (workgroup i runs on XCD i % 8)
 constexpr int BF_WAVES = 8;  // waves of a workgroup: one 32-column frequency tile each (256 columns)
+constexpr int BF_FILL = 3;   // work items wanted per compute unit (of BF_WAVES waves each)
+constexpr int BF_MAXCUT = 8; // most pieces of a row cluster's block list
 constexpr int BF_RTB = 3;    // 32-row tiles of a work item on a row cluster above BF_MC rows (T' from the buffer)
 constexpr int BF_COUNTERS = 4 * BF_NX;   // work counters: lists of far items (small, big row clusters), near items, T' blocks
 constexpr int FRAG = 256;    // uint4 per operator fragment: 4 planes x 64 lanes
@@ -637,50 +639,70 @@ __global__ void __launch_bounds__(KW == 1 ? 512 : 256) bf_rows(
   }
 }
 
-// near blocks of the product: work items (rows of a row cluster, all its
-// inadmissible blocks); each wave owns one 32-row tile and one 32-column
-// frequency tile (BF_WAVES x BF_RT waves: registers for one row tile only, so
-// four waves fit a SIMD); Y += f_d o (D_d X_J) per term; plain stores into the
-// near-field buffer (the level after the tree's deepest)
-__global__ void __launch_bounds__(BF_WAVES * BF_RT * 64) bf_near(
+// near blocks of the product: work items (one 32-row tile of a row cluster, some
+// or all of its inadmissible blocks); each wave owns one 32-column frequency
+// tile, so that the waves of a workgroup take the same operator fragments at
+// about the same time.  Y += f_d o (D_d X_J) per term.  A wave reads X_J once per
+// block, not once per term: BF_NK contraction steps of it (8 column groups, a
+// leaf's width) stay in registers over the block's terms, wider blocks pass in
+// several such pieces.  The operator's next fragment is loaded while the current
+// one is multiplied.  Two waves a SIMD: with four, X_J re-read per term, the
+// kernel was bound by those reads (71 GB per product of the 41k-triangle
+// housing at 256 frequencies; 18.4 -> 11.9 ms there, 4.3 -> 0.85 ms on 3648
+// triangles with the cut block lists below).  Plain stores into a near-field
+// level.
+constexpr int BF_NK = 4;
+__global__ void __launch_bounds__(BF_WAVES * 64, 2) bf_near(
     const BfItem* __restrict__ items, const int* __restrict__ range, const int* __restrict__ rowblk,
     const int* __restrict__ bterm, const int64_t* __restrict__ tfoff, const cpx<float>* __restrict__ pool,
     const BfBlock* __restrict__ bb, const uint4* __restrict__ bfp, const int* __restrict__ colpos, int L, int ng,
     const uint4* __restrict__ Xg, cpx<float>* __restrict__ Ylev, int64_t lev_stride, int* __restrict__ counter,
-    int wk, const int* __restrict__ tmask) {
+    const int* __restrict__ tmask) {
   __shared__ int cur;
   const int lane = threadIdx.x & 63, lr = lane & 31, lh = lane >> 5;
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int wrt = w / wk, wkt = w % wk;   // the wave's row tile and first frequency tile
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
   const int nkt = (L + 31) >> 5;
   int visited = 0;
   for (int it; (it = next_item(range, counter, blockIdx.x % BF_NX, visited, &cur)) >= 0;) {
     const BfItem I = items[it];
-    const int nrt = (I.rows + 31) >> 5;
-    if (wrt >= nrt) continue;   // (next_item's barriers are reached by every wave)
-    const int rt = (I.r0 >> 5) + wrt;
-    for (int kt = wkt; kt < nkt; kt += wk) {
+    const int rt = I.r0 >> 5;
+    for (int kt = w; kt < nkt; kt += nw) {
       if (tmask && !tmask[kt]) continue;
       const Tiles<1> C(kt, nkt, L, lr, ng, colpos, Xg);
       f16v yre = f16_zero(), yim = f16_zero();
       for (int bi = 0; bi < I.nb; ++bi) {
         const int b = rowblk[I.b0 + bi];
         const BfBlock B = bb[b];
-        const uint4* op = bfp + B.off * FRAG;
         const int d0 = bterm[b], nd = bterm[b + 1] - d0;
-        for (int d = 0; d < nd; ++d) {
-          f16v tre = f16_zero(), tim = f16_zero();
-          const uint4* df = op + (int64_t(d) * B.mt + rt) * B.KS * FRAG;
-          for (int j = 0; j < B.KS; ++j) {
-            const int g = 2 * j + lh;
-            const BfGroup3 x = (g < B.G && C.kv[0]) ? load_x(C.xk[0], B.g0 + g, lr) : zero_group3();
-            cstep2(load_op(df + int64_t(j) * FRAG, lane), x, tre, tim);
-          }
-          const cpx<float> f = C.kin[0] ? pool[tfoff[d0 + d] + C.kp[0]] : cpx<float>{0.f, 0.f};
+        const int64_t dstep = int64_t(B.mt) * B.KS * FRAG;   // between two terms' fragments
+        for (int j0 = 0; j0 < B.KS; j0 += BF_NK) {
+          const int ks = min(BF_NK, B.KS - j0);
+          const uint4* df = bfp + B.off * FRAG + (int64_t(rt) * B.KS + j0) * FRAG;
+          BfGroup nxt = load_op(df, lane);
+          BfGroup3 x[BF_NK];
 #pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            yre[r] += f.re * tre[r] - f.im * tim[r];
-            yim[r] += f.re * tim[r] + f.im * tre[r];
+          for (int j = 0; j < BF_NK; ++j) {
+            const int g = 2 * (j0 + j) + lh;
+            x[j] = (j < ks && g < B.G) ? load_x(C.xk[0], B.g0 + g, lr) : zero_group3();
+          }
+          for (int d = 0; d < nd; ++d, df += dstep) {
+            const cpx<float> f = C.kin[0] ? pool[tfoff[d0 + d] + C.kp[0]] : cpx<float>{0.f, 0.f};
+            f16v tre = f16_zero(), tim = f16_zero();
+#pragma unroll
+            for (int j = 0; j < BF_NK; ++j) {
+              if (j >= ks) break;
+              const BfGroup a = nxt;
+              if (j + 1 < ks)
+                nxt = load_op(df + (j + 1) * FRAG, lane);
+              else if (d + 1 < nd)
+                nxt = load_op(df + dstep, lane);
+              cstep2(a, x[j], tre, tim);
+            }
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+              yre[r] += f.re * tre[r] - f.im * tim[r];
+              yim[r] += f.re * tim[r] + f.im * tre[r];
+            }
           }
         }
       }
@@ -688,7 +710,7 @@ __global__ void __launch_bounds__(BF_WAVES * BF_RT * 64) bf_near(
         cpx<float>* yl = Ylev + I.lev * lev_stride;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const int row = 32 * wrt + 8 * (r >> 2) + 4 * lh + (r & 3);
+          const int row = 8 * (r >> 2) + 4 * lh + (r & 3);
           if (row < I.rows) yl[int64_t(I.rb + I.r0 + row) * L + C.kcol[0]] = {yre[r], yim[r]};
         }
       }
@@ -699,16 +721,16 @@ __global__ void __launch_bounds__(BF_WAVES * BF_RT * 64) bf_near(
 // Y[k][perm[p]] = sum over the levels of row p's row clusters (conjugated for
 // conjugate-represented columns)
 __global__ void bf_reduce_out(const cpx<float>* __restrict__ Ylev, int64_t lev_stride,
-                              const unsigned* __restrict__ mask, cpx<float>* __restrict__ Y,
+                              const unsigned long long* __restrict__ mask, cpx<float>* __restrict__ Y,
                               const int* __restrict__ perm, const int* __restrict__ conjflag, int n, int L) {
   const int64_t total = int64_t(n) * L;
   for (int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; e < total;
        e += int64_t(gridDim.x) * blockDim.x) {
     const int p = int(e / L), k = int(e % L);
-    unsigned msk = mask[p];
+    unsigned long long msk = mask[p];
     float re = 0.f, im = 0.f;
     while (msk) {
-      const int d = __builtin_ctz(msk);
+      const int d = __builtin_ctzll(msk);
       msk &= msk - 1;
       const cpx<float> v = Ylev[d * lev_stride + e];
       re += v.re;
@@ -766,7 +788,7 @@ int bf16_setup(gcq_context* ctx) {
   }
   // work items: per row cluster, chunks of BF_MC rows with all its far blocks
   // (far items, stored into the level of the cluster's depth) and with all its
-  // near blocks (near items, stored into the level after the deepest)
+  // near blocks (near items, stored into levels after the deepest)
   int nlev = 0;
   for (auto& C : ctx->clusters) nlev = std::max(nlev, C.depth + 1);
   if (nlev > 31) return fail(GCQ_ERR_UNSUPPORTED, "cluster tree deeper than 31 levels");
@@ -780,46 +802,87 @@ int bf16_setup(gcq_context* ctx) {
     const int kind = ctx->blocks[b].admissible ? (bb[b].toff >= 0 ? 1 : 0) : 2;
     byrow[kind][r].push_back(b);
   }
+  // (Near items of different depths have levels of their own too: a leaf next to a
+  // cluster that is split further makes near blocks of both that cluster's rows
+  // and its sons'.)
+  // A small partition has fewer row tiles than the chip has places for
+  // workgroups (64 row clusters at 3648 triangles): there the blocks of a row
+  // cluster are cut into up to `split` items, each of which stores into a level
+  // of its own, so that BF_FILL items come for every compute unit's share of
+  // waves (near items at 256 frequencies on 3648 triangles: 4.3 ms in one piece).
   std::vector<int> rowblk;
   std::vector<BfItem> sitems;
   std::vector<int> range;   // BF_NX + 1 bounds of the lists of each kind
-  std::vector<unsigned> mask(n, 0u);
+  std::vector<unsigned long long> mask(n, 0ull);
+  int levels = nlev;        // levels used: the tree's depths (far items), then the near items' and the cuts'
   for (int kind = 0; kind < 3; ++kind) {
     std::vector<BfItem> items;
     std::vector<double> cost;
-    const int chunk = kind == 1 ? 32 * BF_RTB : BF_MC;
+    const int chunk = kind == 0 ? BF_MC : kind == 1 ? 32 * BF_RTB : 32;
+    int64_t tiles = 0;
+    std::vector<char> used(nlev, 0);   // depths with items of this kind
+    for (size_t c = 0; c < byrow[kind].size(); ++c) {
+      if (byrow[kind][c].empty()) continue;
+      tiles += (ctx->clusters[c].end - ctx->clusters[c].begin + chunk - 1) / chunk;
+      used[ctx->clusters[c].depth] = 1;
+    }
+    const int depths = int(std::count(used.begin(), used.end(), 1));
+    const int64_t want = int64_t(ctx->cus) * BF_FILL * BF_WAVES / std::min(BF_WAVES, nkt);
+    int split = 1;
+    if (kind != 1 && tiles > 0)
+      split = int(std::min<int64_t>((want + tiles - 1) / tiles, BF_MAXCUT));
+    // levels: the first cut of a far item in its depth's, every other one in its own;
+    // the row mask holds 64 (a tree has at most 31 depths, and as many may hold
+    // near blocks)
+    while (split > 1 && levels + depths * split > (kind == 0 ? 32 : 64)) --split;
+    std::vector<int> extra(nlev, 0);   // first added level of each depth
+    for (int d = 0; d < nlev; ++d)
+      if (used[d]) {
+        extra[d] = levels;
+        levels += split - (kind == 2 ? 0 : 1);
+      }
     for (size_t c = 0; c < byrow[kind].size(); ++c) {
       const std::vector<int>& bl = byrow[kind][c];
       if (bl.empty()) continue;
       const Cluster& A = ctx->clusters[c];
       const int m = A.end - A.begin;
-      const int lev = kind < 2 ? A.depth : nlev;
-      for (int p = A.begin; p < A.end; ++p) mask[p] |= 1u << lev;
       const int b0 = int(rowblk.size());
       rowblk.insert(rowblk.end(), bl.begin(), bl.end());
-      for (int r0 = 0; r0 < m; r0 += chunk) {
-        BfItem it;
-        it.b0 = b0;
-        it.nb = int(bl.size());
-        it.rb = A.begin;
-        it.m = m;
-        it.r0 = r0;
-        it.rows = std::min(chunk, m - r0);
-        it.lev = lev;
-        it.pad = 0;
-        const int nrt = (it.rows + 31) / 32;
-        double wk = 0;
-        for (int b : bl) {
-          const BfBlock& x = bb[b];
-          if (kind == 0)
-            wk += double(x.T) * (x.KS + 2 * nrt);
-          else if (kind == 1)
-            wk += double(x.T) * 3 * nrt;
-          else
-            wk += double(F.brank[b]) * nrt * x.KS;
+      auto work_of = [&](int b, int nrt) {
+        const BfBlock& x = bb[b];
+        if (kind == 0) return double(x.T) * (x.KS + 2 * nrt);
+        if (kind == 1) return double(x.T) * 3 * nrt;
+        return double(F.brank[b]) * nrt * x.KS;
+      };
+      // cuts of the block list, of about equal work
+      double all = 0;
+      for (int b : bl) all += work_of(b, 1);
+      const int cuts = std::min(split, int(bl.size()));
+      int lo = 0;
+      double sum = 0;
+      for (int s = 0; s < cuts; ++s) {
+        int hi = lo;
+        while (hi < int(bl.size()) && (hi == lo || s == cuts - 1 || sum < all * (s + 1) / cuts) &&
+               int(bl.size()) - hi > cuts - 1 - s)
+          sum += work_of(bl[hi++], 1);
+        const int lev = kind == 2 ? extra[A.depth] + s : s > 0 ? extra[A.depth] + s - 1 : A.depth;
+        for (int p = A.begin; p < A.end; ++p) mask[p] |= 1ull << lev;
+        for (int r0 = 0; r0 < m; r0 += chunk) {
+          BfItem it;
+          it.b0 = b0 + lo;
+          it.nb = hi - lo;
+          it.rb = A.begin;
+          it.m = m;
+          it.r0 = r0;
+          it.rows = std::min(chunk, m - r0);
+          it.lev = lev;
+          it.pad = 0;
+          double wk = 0;
+          for (int q = lo; q < hi; ++q) wk += work_of(bl[q], (it.rows + 31) / 32);
+          items.push_back(it);
+          cost.push_back(wk);
         }
-        items.push_back(it);
-        cost.push_back(wk);
+        lo = hi;
       }
     }
     // spatial order (first row), cut into BF_NX consecutive lists of equal cost
@@ -872,7 +935,7 @@ int bf16_setup(gcq_context* ctx) {
   GCQ_HIP(hipStreamSynchronize(ctx->stream));
   F.bf_items = int(sitems.size());
   F.bf_big = int(big.size());
-  F.bf_levels = nlev + 1;
+  F.bf_levels = levels;
   F.bf_bytes = off * FRAG * int64_t(sizeof(uint4));
   F.bf_valid = true;
   return GCQ_OK;
@@ -913,12 +976,12 @@ static void enqueue_bf_kernels(gcq_context* ctx, hipStream_t st, const uint4* Xg
                      range + BF_NX + 1, F.d_bfrowblk.as<int>(), F.d_cols.as<int64_t>(), F.d_bcol.as<int>(),
                      F.slices.as<cpx<float>>(), F.d_bfblk.as<BfBlock>(), F.bfpool.as<uint4>(), d_colpos, L, ng,
                      Xg, F.bftbuf.as<uint4>(), Ylev, lev_stride, counter + BF_NX, tmask);
-  // near blocks: one frequency tile and one row tile per wave
+  // near blocks: one frequency tile per wave, two waves a SIMD
   const int nwk = std::min(BF_WAVES, nkt);
-  hipLaunchKernelGGL(bf_near, dim3(ctx->cus * 2), dim3(64 * nwk * BF_RT), 0, st, F.d_bfitems.as<BfItem>(),
+  hipLaunchKernelGGL(bf_near, dim3(ctx->cus * (BF_WAVES / nwk)), dim3(64 * nwk), 0, st, F.d_bfitems.as<BfItem>(),
                      range + 2 * (BF_NX + 1), F.d_bfrowblk.as<int>(), F.d_bterm.as<int>(), F.d_tfoff.as<int64_t>(),
                      F.slices.as<cpx<float>>(), F.d_bfblk.as<BfBlock>(), F.bfpool.as<uint4>(), d_colpos, L, ng, Xg,
-                     Ylev, lev_stride, counter + 2 * BF_NX, nwk, tmask);
+                     Ylev, lev_stride, counter + 2 * BF_NX, tmask);
 }
 
 // kernels of one product on stream st (no allocation, no host transfer)
@@ -939,7 +1002,7 @@ void enqueue_perfreq_bf16(gcq_context* ctx, hipStream_t st, const void* X, void*
     enqueue_bf_kernels<2>(ctx, st, Xg, counter, Ylev, lev_stride, d_colpos, tile_mask);
   else
     enqueue_bf_kernels<1>(ctx, st, Xg, counter, Ylev, lev_stride, d_colpos, tile_mask);
-  hipLaunchKernelGGL(bf_reduce_out, dim3(4096), dim3(256), 0, st, Ylev, lev_stride, F.d_bfmask.as<unsigned>(),
+  hipLaunchKernelGGL(bf_reduce_out, dim3(4096), dim3(256), 0, st, Ylev, lev_stride, F.d_bfmask.as<unsigned long long>(),
                      (cpx<float>*)Y, perm, d_conj, n, L);
 }
 
