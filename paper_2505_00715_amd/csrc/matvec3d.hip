@@ -423,86 +423,164 @@ __global__ void __launch_bounds__(256) perfreq_mfma(
   }
 }
 
-// eq. product: one wave per block; per slice the frequency sums w1 (plain
-// columns) and w2 (conjugate-represented columns, conjugated input) are formed
-// first, then y_I += H w1 + conj(H w2)
+// eq. product: a workgroup of four waves per block, up to WS_D terms of it at a
+// time.  Per piece of WS_J columns the frequency sums w1_d (plain columns) and
+// w2_d (conjugate-represented columns, conjugated input) of all those terms form
+// in one pass over X (the fibers staged in LDS, the frequencies dealt to the
+// threads that a narrow block leaves over); then y_I += sum_d H_d w1_d +
+// conj(H_d w2_d), a far block through its stacked factors: t = Vbar^H w, 16
+// lanes a column, and y = Ubar t, a thread a row.  Bound by the stored slices'
+// bytes, each read once (one wave per block and one term at a time, which read X
+// anew for every term, took 11.4 ms on the 20480-triangle sphere at 64
+// frequencies; now 3.6).  Accumulation into y with atomics.
+constexpr int WS_D = 8, WS_J = 128, WS_K = 64, WS_R = WS_D * 64;
 template <typename T>
-__global__ void __launch_bounds__(64) wsum_kernel(
+__global__ void __launch_bounds__(256) wsum_kernel(
     const int* __restrict__ blk, const int* __restrict__ order, int nblocks, const int* __restrict__ bterm,
     const int* __restrict__ trank, const int64_t* __restrict__ toff,
     const int64_t* __restrict__ tvoff, const int64_t* __restrict__ tfoff,
     const cpx<T>* __restrict__ pool, const int* __restrict__ colpos,
     const int* __restrict__ conjf, int L, int n,
-    const cpx<T>* __restrict__ X, cpx<T>* __restrict__ ybuf, cpx<T>* __restrict__ scratch,
-    int64_t sstride) {
-  __shared__ cpx<T> t1[64], t2[64];
-  const int lane = threadIdx.x;
-  cpx<T>* w1 = scratch + int64_t(blockIdx.x) * sstride;
+    const cpx<T>* __restrict__ X, cpx<T>* __restrict__ ybuf) {
+  __shared__ cpx<T> ws[2][WS_D][WS_J];
+  __shared__ cpx<T> fs[WS_D][WS_K];
+  __shared__ cpx<T> ts[2][WS_R];
+  __shared__ cpx<T> red[256];
+  __shared__ unsigned char cterm[WS_R];
+  __shared__ unsigned char cj[WS_K];
+  const int tid = threadIdx.x;
   for (int ob = blockIdx.x; ob < nblocks; ob += gridDim.x) {
     const int b = order[ob];   // blocks with terms, most work first
     const int rb = blk[5 * b], m = blk[5 * b + 1] - rb, cb = blk[5 * b + 2], nn = blk[5 * b + 3] - cb;
-    cpx<T>* w2 = w1 + nn;
-    for (int d = bterm[b]; d < bterm[b + 1]; ++d) {
-      const cpx<T>* f = pool + tfoff[d];
-      __syncthreads();
-      for (int j = lane; j < nn; j += WAVE) {
-        cpx<T> a1 = {0, 0}, a2 = {0, 0};
-        for (int k = 0; k < L; ++k) {
-          cpx<T> xv = X[int64_t(k) * n + cb + j];  // X in cluster order, not conjugated
-          cpx<T> fk = f[colpos[k]];
-          if (conjf[k]) {
-            cpx<T> p = cmul(fk, cpx<T>{xv.re, -xv.im});
-            a2.re += p.re;
-            a2.im += p.im;
-          } else {
-            cpx<T> p = cmul(fk, xv);
-            a1.re += p.re;
-            a1.im += p.im;
-          }
+    const bool far = trank[bterm[b]] >= 0;
+    const int jt = nn <= 64 ? 64 : WS_J, kg = tid / jt, nkg = 256 / jt, jl = tid % jt;
+    const int it = m <= 64 ? 64 : m <= 128 ? 128 : 256, ig = tid / it, nig = 256 / it;
+    for (int d0 = bterm[b]; d0 < bterm[b + 1]; d0 += WS_D) {
+      const int nd = min(WS_D, bterm[b + 1] - d0);
+      int R = 0;
+      __syncthreads();   // the last piece's readers are done
+      if (far)
+        for (int d = 0; d < nd; ++d) {
+          const int r = trank[d0 + d];
+          for (int c = tid; c < r; c += 256) cterm[R + c] = (unsigned char)d;
+          R += r;
         }
-        w1[j] = a1;
-        w2[j] = a2;
-      }
-      __syncthreads();
-      const int t = trank[d];
-      const cpx<T>* S = pool + toff[d];
-      if (t < 0) {
-        for (int i = lane; i < m; i += WAVE) {
-          cpx<T> s1 = {0, 0}, s2 = {0, 0};
-          for (int j = 0; j < nn; ++j) {
-            cpx<T> h = S[int64_t(j) * m + i];
-            cpx<T> p1 = cmul(h, w1[j]), p2 = cmul(h, w2[j]);
-            s1.re += p1.re; s1.im += p1.im;
-            s2.re += p2.re; s2.im += p2.im;
+      for (int j0 = 0; j0 < nn; j0 += WS_J) {
+        const int jn = min(WS_J, nn - j0);
+        cpx<T> a1[WS_D], a2[WS_D];
+#pragma unroll
+        for (int d = 0; d < WS_D; ++d) a1[d] = a2[d] = {T(0), T(0)};
+        for (int k0 = 0; k0 < L; k0 += WS_K) {
+          const int kn = min(WS_K, L - k0);
+          __syncthreads();
+          for (int e = tid; e < WS_D * WS_K; e += 256) {
+            const int d = e / WS_K, k = e % WS_K;
+            fs[d][k] = (d < nd && k < kn) ? pool[tfoff[d0 + d] + colpos[k0 + k]] : cpx<T>{T(0), T(0)};
           }
-          atomicAdd(&ybuf[rb + i].re, s1.re + s2.re);
-          atomicAdd(&ybuf[rb + i].im, s1.im - s2.im);
+          if (tid < kn) cj[tid] = (unsigned char)conjf[k0 + tid];
+          __syncthreads();
+          if (jl < jn)
+            for (int k = kg; k < kn; k += nkg) {
+              const cpx<T> x = X[int64_t(k0 + k) * n + cb + j0 + jl];   // cluster order, not conjugated
+              if (uni(cj[k])) {
+#pragma unroll
+                for (int d = 0; d < WS_D; ++d) {
+                  const cpx<T> f = fs[d][k];
+                  a2[d].re += f.re * x.re + f.im * x.im;   // f conj(x)
+                  a2[d].im += f.im * x.re - f.re * x.im;
+                }
+              } else {
+#pragma unroll
+                for (int d = 0; d < WS_D; ++d) {
+                  const cpx<T> f = fs[d][k];
+                  a1[d].re += f.re * x.re - f.im * x.im;
+                  a1[d].im += f.re * x.im + f.im * x.re;
+                }
+              }
+            }
         }
-      } else {
-        const cpx<T>* V = pool + tvoff[d];
-        for (int c = 0; c < t; ++c) {
-          T r1 = 0, i1 = 0, r2 = 0, i2 = 0;
-          for (int j = lane; j < nn; j += WAVE) {
-            cpx<T> v = V[int64_t(c) * nn + j];
-            cpx<T> p1 = cmulc(v, w1[j]), p2 = cmulc(v, w2[j]);
-            r1 += p1.re; i1 += p1.im;
-            r2 += p2.re; i2 += p2.im;
-          }
-          r1 = wave_sum(r1); i1 = wave_sum(i1);
-          r2 = wave_sum(r2); i2 = wave_sum(i2);
-          if (lane == 0) { t1[c] = {r1, i1}; t2[c] = {r2, i2}; }
+        for (int g = 0; g < nkg; ++g) {   // the frequency groups' sums, in group order
+          if (kg == g)
+#pragma unroll
+            for (int d = 0; d < WS_D; ++d) {
+              const cpx<T> o1 = g ? ws[0][d][jl] : cpx<T>{T(0), T(0)}, o2 = g ? ws[1][d][jl] : cpx<T>{T(0), T(0)};
+              ws[0][d][jl] = {o1.re + a1[d].re, o1.im + a1[d].im};
+              ws[1][d][jl] = {o2.re + a2[d].re, o2.im + a2[d].im};
+            }
+          __syncthreads();
         }
-        __syncthreads();
-        for (int i = lane; i < m; i += WAVE) {
-          cpx<T> s1 = {0, 0}, s2 = {0, 0};
-          for (int c = 0; c < t; ++c) {
-            cpx<T> u = S[int64_t(c) * m + i];
-            cpx<T> p1 = cmul(u, t1[c]), p2 = cmul(u, t2[c]);
-            s1.re += p1.re; s1.im += p1.im;
-            s2.re += p2.re; s2.im += p2.im;
+        if (far) {
+          // t[c] over this piece of columns, 16 lanes a column
+          const cpx<T>* V = pool + tvoff[d0] + j0;
+          const int q = tid & 15;
+          for (int c = tid >> 4; c < R; c += 16) {
+            const int d = cterm[c];
+            const cpx<T>* Vc = V + int64_t(c) * nn;
+            T r1 = 0, i1 = 0, r2 = 0, i2 = 0;
+            for (int j = q; j < jn; j += 16) {
+              const cpx<T> v = Vc[j], p1 = cmulc(v, ws[0][d][j]), p2 = cmulc(v, ws[1][d][j]);
+              r1 += p1.re; i1 += p1.im;
+              r2 += p2.re; i2 += p2.im;
+            }
+#pragma unroll
+            for (int o = 8; o > 0; o >>= 1) {
+              r1 += __shfl_xor(r1, o, WAVE);
+              i1 += __shfl_xor(i1, o, WAVE);
+              r2 += __shfl_xor(r2, o, WAVE);
+              i2 += __shfl_xor(i2, o, WAVE);
+            }
+            if (q == 0) {
+              const cpx<T> o1 = j0 ? ts[0][c] : cpx<T>{T(0), T(0)}, o2 = j0 ? ts[1][c] : cpx<T>{T(0), T(0)};
+              ts[0][c] = {o1.re + r1, o1.im + i1};
+              ts[1][c] = {o2.re + r2, o2.im + i2};
+            }
           }
-          atomicAdd(&ybuf[rb + i].re, s1.re + s2.re);
-          atomicAdd(&ybuf[rb + i].im, s1.im - s2.im);
+          if (j0 + WS_J < nn) continue;
+          __syncthreads();
+        }
+        // rows: far from all columns' t, near from this piece's w
+        for (int i0 = 0; i0 < m; i0 += it) {
+          const int i = i0 + tid % it;
+          T re = 0, im = 0;
+          if (i < m) {
+            if (far) {
+              const cpx<T>* U = pool + toff[d0] + i;
+              T r2 = 0, i2 = 0;
+              for (int c = ig; c < R; c += nig) {
+                const cpx<T> u = U[int64_t(c) * m], p1 = cmul(u, ts[0][c]), p2 = cmul(u, ts[1][c]);
+                re += p1.re; im += p1.im;
+                r2 += p2.re; i2 += p2.im;
+              }
+              re += r2;
+              im -= i2;
+            } else {
+              T r2 = 0, i2 = 0;
+              for (int d = 0; d < nd; ++d) {
+                const cpx<T>* D = pool + toff[d0 + d] + int64_t(j0) * m + i;
+                for (int j = ig; j < jn; j += nig) {
+                  const cpx<T> h = D[int64_t(j) * m], p1 = cmul(h, ws[0][d][j]), p2 = cmul(h, ws[1][d][j]);
+                  re += p1.re; im += p1.im;
+                  r2 += p2.re; i2 += p2.im;
+                }
+              }
+              re += r2;
+              im -= i2;
+            }
+          }
+          if (nig > 1) {
+            red[tid] = {re, im};
+            __syncthreads();
+            if (ig == 0)
+              for (int g = 1; g < nig; ++g) {
+                re += red[g * it + tid].re;
+                im += red[g * it + tid].im;
+              }
+            __syncthreads();
+          }
+          if (ig == 0 && i < m) {
+            atomicAdd(&ybuf[rb + i].re, re);
+            atomicAdd(&ybuf[rb + i].im, im);
+          }
         }
       }
     }
@@ -628,12 +706,9 @@ static int compressed_impl(gcq_context* ctx, int mode, int precision, const void
   const int* d_colpos = ctx->scratchC.as<int>();
   const int* d_conj = d_colpos + L;
   const int64_t nl = int64_t(n) * L;
-  int maxn = 0;
-  for (auto& B : ctx->blocks)
-    maxn = std::max(maxn, ctx->clusters[B.col].end - ctx->clusters[B.col].begin);
   const int nmv = F.n_mvblocks;
   const int wgrid = std::max(1, std::min(nmv, ctx->cus * 32));
-  GCQ_TRY(ctx->scratchB.ensure(size_t(nl + n + 2 * int64_t(maxn) * wgrid) * sizeof(cpx<T>)));
+  GCQ_TRY(ctx->scratchB.ensure(size_t(nl + n) * sizeof(cpx<T>)));
   cpx<T>* Xp = ctx->scratchB.as<cpx<T>>();
   cpx<T>* Yp = Xp + nl;
   const int g = 4096;
@@ -650,12 +725,11 @@ static int compressed_impl(gcq_context* ctx, int mode, int precision, const void
       hipLaunchKernelGGL((perm_in3<float, T>), dim3(g), dim3(256), 0, st, (const cpx<float>*)X, Xp,
                          perm, ctx->scratchD.as<int>(), n, L);
     hipLaunchKernelGGL(zero3<T>, dim3(64), dim3(256), 0, st, Yp, int64_t(n));
-    hipLaunchKernelGGL(wsum_kernel<T>, dim3(wgrid), dim3(64), 0, st, ctx->d_blk.as<int>(),
+    hipLaunchKernelGGL(wsum_kernel<T>, dim3(wgrid), dim3(256), 0, st, ctx->d_blk.as<int>(),
                        F.d_mvorder.as<int>(), nmv,
                        F.d_bterm.as<int>(), F.d_trank.as<int>(), F.d_toff.as<int64_t>(),
                        F.d_tvoff.as<int64_t>(), F.d_tfoff.as<int64_t>(), F.slices.as<cpx<T>>(),
-                       d_colpos, d_conj, L, n, Xp,
-                       Yp, Yp + n, int64_t(2) * maxn);
+                       d_colpos, d_conj, L, n, Xp, Yp);
     if (precision == GCQ_C128)
       hipLaunchKernelGGL((perm_out3<T, double>), dim3(64), dim3(256), 0, st, Yp, (cpx<double>*)Y,
                          perm, ctx->scratchD.as<int>(), n, 1);
