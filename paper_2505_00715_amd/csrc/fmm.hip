@@ -26,7 +26,7 @@
 namespace gcq {
 
 constexpr int FMM_PMAX = 6;       // nodes per dimension
-constexpr int FMM_RC = 8;         // rows of the M2L output a workgroup owns
+constexpr int FMM_RC = 8;         // rows of the M2L output a workgroup owns (double)
 constexpr double FMM_MIN_HALF = 1e-3;
 
 // ---- host: interpolation tables --------------------------------------------------------
@@ -126,6 +126,9 @@ __global__ void fmm_x_in(const cpx<T>* __restrict__ X, cpx<T>* __restrict__ Xp, 
   }
 }
 
+// The level kernels (P2M, M2M, L2L, L2P) give a cluster's outputs to gridDim.y
+// workgroups: a level near the root has one to a few clusters, which a workgroup
+// each took 0.54 ms a level (M2M, 64 nodes x 128 frequencies; now 0.055).
 // P2M: W[c][m][k] = sum_{p in leaf c} R[p][m] Xp[p][k]
 template <typename T>
 __global__ void __launch_bounds__(256) fmm_p2m(const int* __restrict__ leaves, int nleaves,
@@ -134,7 +137,7 @@ __global__ void __launch_bounds__(256) fmm_p2m(const int* __restrict__ leaves, i
                                                cpx<T>* __restrict__ W, int np3, int L) {
   for (int q = blockIdx.x; q < nleaves; q += gridDim.x) {
     const int c = leaves[q], b = clbeg[c], e1 = clend[c];
-    for (int e = threadIdx.x; e < np3 * L; e += blockDim.x) {
+    for (int e = blockIdx.y * 256 + threadIdx.x; e < np3 * L; e += gridDim.y * 256) {
       const int m = e / L, k = e % L;
       cpx<T> acc = {T(0), T(0)};
       for (int pp = b; pp < e1; ++pp) {
@@ -156,7 +159,7 @@ __global__ void __launch_bounds__(256) fmm_m2m(const int* __restrict__ list, int
   for (int q = blockIdx.x; q < cnt; q += gridDim.x) {
     const int c = list[q];
     const int s[2] = {son0[c], son1[c]};
-    for (int e = threadIdx.x; e < np3 * L; e += blockDim.x) {
+    for (int e = blockIdx.y * 256 + threadIdx.x; e < np3 * L; e += gridDim.y * 256) {
       const int mp = e / L, k = e % L;
       cpx<T> acc = {T(0), T(0)};
       for (int h = 0; h < 2; ++h) {
@@ -237,6 +240,108 @@ __global__ void __launch_bounds__(256) fmm_m2l(const FmmItem* __restrict__ items
   }
 }
 
+// The M2L of float expansions on the matrix cores (v_mfma_f32_32x32x2f32; A[i][k]
+// in lane i + 32 k, B[k][j] in lane j + 32 k, D[8 (r / 4) + 4 (l / 32) + r % 4][l % 32]
+// in element r of lane l): a wave owns 32 rows of an item's local expansion and
+// 32 frequency columns.  W[Y] of a block stays in registers over its terms
+// (FMM_MC nodes; larger orders pass in pieces of the contraction), a complex step
+// takes four real products, and the next FMM_KU steps' slice values are loaded
+// while the current ones are multiplied.  The waves of one item (its frequency
+// tiles) have workgroup numbers 8 apart, so that they run on one XCD and share
+// the slices in its L2.  Bound by the matrix cores (2.8 ms of products at the
+// float rate for 11232 triangles, order 4, 128 frequencies; 22.4 ms on the vector
+// units with W[Y] read per term, now 4.5).
+typedef float fm_v16 __attribute__((ext_vector_type(16)));
+constexpr int FMM_RT = 32;    // rows of an item (matrix cores)
+constexpr int FMM_MC = 64;    // nodes of W[Y] held in registers
+constexpr int FMM_KU = 8;     // contraction steps (of 2 nodes) loaded ahead
+
+__device__ __forceinline__ fm_v16 fm_mul(float a, float b, fm_v16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+}
+
+__global__ void __launch_bounds__(64, 2) fmm_m2l_mfma(const FmmItem* __restrict__ items, int nitems,
+                                                      const int* __restrict__ rowlist, const int* __restrict__ fcol,
+                                                      const int* __restrict__ fstart,
+                                                      const int64_t* __restrict__ fslice,
+                                                      const int64_t* __restrict__ ffiber,
+                                                      const cpx<float>* __restrict__ pool,
+                                                      const int* __restrict__ kpos, const cpx<float>* __restrict__ W,
+                                                      cpx<float>* __restrict__ Z, int np3, int L) {
+  const int nkt = (L + 31) >> 5;
+  const int loc = blockIdx.x >> 3, it = (loc / nkt) * 8 + (blockIdx.x & 7), kt = loc % nkt;
+  if (it >= nitems) return;
+  const FmmItem I = items[it];
+  const int lane = threadIdx.x, lr = lane & 31, lh = lane >> 5;
+  const int k = kt * 32 + lr;
+  const bool kin = k < L;
+  const int kp = kin ? kpos[k] : 0, kc = kin ? k : L - 1;
+  const int row = I.r0 + lr;
+  const int rc = min(row, np3 - 1);   // rows beyond np3 multiply, and are not stored
+  fm_v16 zre, zim;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) zre[r] = zim[r] = 0.f;
+  for (int bi = 0; bi < I.nb; ++bi) {
+    const int f = rowlist[I.b0 + bi];
+    const cpx<float>* wy = W + int64_t(fcol[f]) * np3 * L + kc;
+    const int d0 = fstart[f], d1 = fstart[f + 1];
+    for (int m0 = 0; m0 < np3; m0 += FMM_MC) {
+      const int mn = min(FMM_MC, np3 - m0);
+      cpx<float> w[FMM_MC / 2];
+#pragma unroll
+      for (int s = 0; s < FMM_MC / 2; ++s) {
+        const int m = 2 * s + lh;
+        w[s] = wy[(m0 + min(m, mn - 1)) * L];
+        if (m >= mn) w[s] = {0.f, 0.f};
+      }
+      cpx<float> a[FMM_KU];
+      const cpx<float>* H = pool + fslice[d0] + int64_t(m0) * np3 + rc;
+#pragma unroll
+      for (int u = 0; u < FMM_KU; ++u) a[u] = H[min(2 * u + lh, mn - 1) * np3];
+      for (int d = d0; d < d1; ++d) {
+        const cpx<float> fk = pool[ffiber[d] + kp];
+        const cpx<float>* Hn = d + 1 < d1 ? pool + fslice[d + 1] + int64_t(m0) * np3 + rc : H;
+        fm_v16 tre, tim;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) tre[r] = tim[r] = 0.f;
+#pragma unroll
+        for (int s0 = 0; s0 < FMM_MC / 2; s0 += FMM_KU) {
+          if (2 * s0 >= mn) break;
+          cpx<float> c[FMM_KU];
+          const bool last = 2 * (s0 + FMM_KU) >= mn;
+          const cpx<float>* P = last ? Hn : H;
+          const int mb = last ? 0 : 2 * (s0 + FMM_KU);
+#pragma unroll
+          for (int u = 0; u < FMM_KU; ++u) {
+            c[u] = a[u];
+            a[u] = P[min(mb + 2 * u + lh, mn - 1) * np3];
+          }
+#pragma unroll
+          for (int u = 0; u < FMM_KU; ++u) {
+            const cpx<float> x = w[s0 + u];
+            tre = fm_mul(c[u].re, x.re, tre);
+            tim = fm_mul(c[u].re, x.im, tim);
+            tre = fm_mul(-c[u].im, x.im, tre);
+            tim = fm_mul(c[u].im, x.re, tim);
+          }
+        }
+        H = Hn;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          zre[r] += fk.re * tre[r] - fk.im * tim[r];
+          zim[r] += fk.re * tim[r] + fk.im * tre[r];
+        }
+      }
+    }
+  }
+  if (kin)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int i = I.r0 + 8 * (r >> 2) + 4 * lh + (r & 3);
+      if (i < np3) Z[(int64_t(I.X) * np3 + i) * L + k] = {zre[r], zim[r]};
+    }
+}
+
 // zero the local expansions of the clusters that receive no M2L term
 template <typename T>
 __global__ void fmm_zero(const int* __restrict__ list, int cnt, cpx<T>* __restrict__ Z, int np3, int L) {
@@ -254,7 +359,7 @@ __global__ void __launch_bounds__(256) fmm_l2l(const int* __restrict__ list, int
     const int c = list[q], P = parent[c];
     const T* tc = Tr + int64_t(c) * np3 * np3;
     const cpx<T>* zp = Z + int64_t(P) * np3 * L;
-    for (int e = threadIdx.x; e < np3 * L; e += blockDim.x) {
+    for (int e = blockIdx.y * 256 + threadIdx.x; e < np3 * L; e += gridDim.y * 256) {
       const int m = e / L, k = e % L;
       cpx<T> acc = Z[(int64_t(c) * np3 + m) * L + k];
       for (int mp = 0; mp < np3; ++mp) {
@@ -279,7 +384,7 @@ __global__ void __launch_bounds__(256) fmm_l2p(const int* __restrict__ leaves, i
   for (int q = blockIdx.x; q < nleaves; q += gridDim.x) {
     const int c = leaves[q], b = clbeg[c], e1 = clend[c];
     const cpx<T>* zc = Z + int64_t(c) * np3 * L;
-    for (int e = threadIdx.x; e < (e1 - b) * L; e += blockDim.x) {
+    for (int e = blockIdx.y * 256 + threadIdx.x; e < (e1 - b) * L; e += gridDim.y * 256) {
       const int pp = b + e / L, k = e % L;
       cpx<T> acc = {T(0), T(0)};
       for (int nn = 0; nn < np3; ++nn) {
@@ -359,33 +464,46 @@ static void fmm_far_product(gcq_context* ctx, const void* X, void* Y) {
   cpx<T>* Z = M.Z.as<cpx<T>>();
   const int* conjf = M.d_conj.as<int>();
   const int grid = ctx->cus * 4;
+  // workgroups per cluster of a level of cnt clusters: enough for the chip, at
+  // most one output a thread
+  auto level = [&](int cnt, int64_t outputs) {
+    const int y = int(std::min<int64_t>((outputs + 255) / 256, std::max(1, ctx->cus * 8 / std::max(cnt, 1))));
+    return dim3(std::min(cnt, grid), std::max(y, 1));
+  };
   hipLaunchKernelGGL(fmm_x_in<T>, dim3(4096), dim3(256), 0, st, static_cast<const cpx<T>*>(X), Xp,
                      ctx->d_perm.as<int>(), conjf, n, L);
-  hipLaunchKernelGGL(fmm_p2m<T>, dim3(std::min(M.nleaves, grid)), dim3(256), 0, st, M.d_leaves.as<int>(), M.nleaves,
+  hipLaunchKernelGGL(fmm_p2m<T>, level(M.nleaves, int64_t(np3) * L), dim3(256), 0, st, M.d_leaves.as<int>(), M.nleaves,
                      M.d_clbeg.as<int>(), M.d_clend.as<int>(), M.d_R.as<T>(), Xp, W, np3, L);
   // upward: levels from the deepest, clusters with sons
   for (int lev = int(M.lev_start.size()) - 2; lev >= 0; --lev) {
     const int c0 = M.lev_start[lev], cnt = M.lev_start[lev + 1] - c0;
     if (cnt > 0)
-      hipLaunchKernelGGL(fmm_m2m<T>, dim3(std::min(cnt, grid)), dim3(256), 0, st, M.d_uplist.as<int>() + c0, cnt,
+      hipLaunchKernelGGL(fmm_m2m<T>, level(cnt, int64_t(np3) * L), dim3(256), 0, st, M.d_uplist.as<int>() + c0, cnt,
                          M.d_son0.as<int>(), M.d_son1.as<int>(), M.d_T.as<T>(), W, np3, L);
   }
   if (M.nzero > 0)
     hipLaunchKernelGGL(fmm_zero<T>, dim3(std::min(M.nzero, grid)), dim3(256), 0, st, M.d_zlist.as<int>(), M.nzero,
                        Z, np3, L);
-  if (M.nitems > 0)
-    hipLaunchKernelGGL(fmm_m2l<T>, dim3(std::min(M.nitems, grid * 2)), dim3(256), 0, st, M.d_items.as<FmmItem>(),
-                       M.nitems, M.d_rowlist.as<int>(), M.d_fcol.as<int>(), M.d_fstart.as<int>(),
-                       M.d_fslice.as<int64_t>(), M.d_ffiber.as<int64_t>(), M.pool.as<cpx<T>>(),
-                       M.d_kpos.as<int>(), W, Z, np3, L);
+  if (M.nitems > 0) {
+    if constexpr (sizeof(T) == 4)
+      hipLaunchKernelGGL(fmm_m2l_mfma, dim3((M.nitems + 7) / 8 * 8 * ((L + 31) / 32)), dim3(64), 0, st,
+                         M.d_items.as<FmmItem>(), M.nitems, M.d_rowlist.as<int>(), M.d_fcol.as<int>(),
+                         M.d_fstart.as<int>(), M.d_fslice.as<int64_t>(), M.d_ffiber.as<int64_t>(),
+                         M.pool.as<cpx<float>>(), M.d_kpos.as<int>(), W, Z, np3, L);
+    else
+      hipLaunchKernelGGL(fmm_m2l<T>, dim3(std::min(M.nitems, grid * 2)), dim3(256), 0, st, M.d_items.as<FmmItem>(),
+                         M.nitems, M.d_rowlist.as<int>(), M.d_fcol.as<int>(), M.d_fstart.as<int>(),
+                         M.d_fslice.as<int64_t>(), M.d_ffiber.as<int64_t>(), M.pool.as<cpx<T>>(),
+                         M.d_kpos.as<int>(), W, Z, np3, L);
+  }
   // downward: depth 1 onwards
   for (size_t lev = 1; lev + 1 < M.down_start.size(); ++lev) {
     const int c0 = M.down_start[lev], cnt = M.down_start[lev + 1] - c0;
     if (cnt > 0)
-      hipLaunchKernelGGL(fmm_l2l<T>, dim3(std::min(cnt, grid)), dim3(256), 0, st, M.d_downlist.as<int>() + c0, cnt,
+      hipLaunchKernelGGL(fmm_l2l<T>, level(cnt, int64_t(np3) * L), dim3(256), 0, st, M.d_downlist.as<int>() + c0, cnt,
                          M.d_parent.as<int>(), M.d_T.as<T>(), Z, np3, L);
   }
-  hipLaunchKernelGGL(fmm_l2p<T>, dim3(std::min(M.nleaves, grid)), dim3(256), 0, st, M.d_leaves.as<int>(),
+  hipLaunchKernelGGL(fmm_l2p<T>, level(M.nleaves, int64_t(n) / std::max(M.nleaves, 1) * L), dim3(256), 0, st, M.d_leaves.as<int>(),
                      M.nleaves, M.d_clbeg.as<int>(), M.d_clend.as<int>(), M.d_L.as<T>(), Z, ctx->d_perm.as<int>(),
                      conjf, static_cast<cpx<T>*>(Y), n, np3, L);
 }
@@ -574,7 +692,7 @@ extern "C" GCQ_API int gcq_fmm3d(gcq_context* ctx, int32_t order, double tol, in
     }
     const int b0 = int(rowlist.size());
     rowlist.insert(rowlist.end(), byrow[c].begin(), byrow[c].end());
-    for (int r0 = 0; r0 < np3; r0 += FMM_RC) items.push_back({c, r0, b0, int(byrow[c].size())});
+    for (int r0 = 0; r0 < np3; r0 += (precision == GCQ_C128 ? FMM_RC : FMM_RT)) items.push_back({c, r0, b0, int(byrow[c].size())});
   }
   // most work first
   std::stable_sort(items.begin(), items.end(), [](const FmmItem& a, const FmmItem& b) { return a.nb > b.nb; });
