@@ -1203,6 +1203,18 @@ int aca3d_run(gcq_context* ctx, double tol_aca, double tol, int32_t max_freq_ran
     F.n_mvblocks = int(mo.size());
     GCQ_TRY(upload(F.d_bcol, bcol, ctx->stream));
     GCQ_TRY(upload(F.d_mvorder, mo, ctx->stream));
+    std::vector<int32_t> farlist;
+    std::vector<int2> neartask;
+    for (int b : mo) {
+      if (!bd[b].admissible)
+        for (int i = 0; i < bd[b].m; i += 16) neartask.push_back(make_int2(b, i));
+      else if (bcol[b + 1] > bcol[b])
+        farlist.push_back(b);
+    }
+    F.n_far = int(farlist.size());
+    F.n_neartask = int(neartask.size());
+    GCQ_TRY(upload(F.d_farlist, farlist, ctx->stream));
+    GCQ_TRY(upload(F.d_neartask, neartask, ctx->stream));
     GCQ_TRY(F.d_cols.ensure(sizeof(int64_t) * 3 * size_t(std::max(bcol[nb], 1))));
     hipLaunchKernelGGL(build_cols, dim3(std::min(nb, 65536)), dim3(64), 0, ctx->stream, ctx->d_blk.as<int>(),
                        F.d_bterm.as<int>(), F.d_trank.as<int>(), F.d_toff.as<int64_t>(),

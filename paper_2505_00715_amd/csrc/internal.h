@@ -166,6 +166,10 @@ struct Faces3D {
   // product tables: per far block its stacked columns (U column offset, V
   // column offset, fiber offset), blocks ordered by work, largest first
   DevBuf d_cols, d_bcol, d_mvorder;
+  // the per-frequency product's work: far blocks with stacked columns, and the
+  // near blocks' 16-row tiles (block, first row), both most work first
+  DevBuf d_farlist, d_neartask;
+  int n_far = 0, n_neartask = 0;
   // the product's own buffers: frequency-major copies of X and Y, frequency
   // tables (position in K, conjugation flag); fixed while the operator lives
   DevBuf pxy, pmeta;

@@ -6,9 +6,9 @@
 #include <algorithm>
 #include <cstring>
 
-#include "internal.h"
 #include <type_traits>
 
+#include "internal.h"
 #include "matvec.h"
 
 namespace gcq {
@@ -47,9 +47,9 @@ __global__ void zero3(cpx<T>* p, int64_t n) {
 }
 
 // Xp[p][k] = X[k][perm[p]] (frequency fastest), conjugated for columns applied
-// through their conjugate partner; and the inverse for the result
+// through their conjugate partner, and Yp = 0; and the inverse for the result
 template <typename TI, typename TO>
-__global__ void perm_in_t(const cpx<TI>* __restrict__ X, cpx<TO>* __restrict__ Xp,
+__global__ void perm_in_t(const cpx<TI>* __restrict__ X, cpx<TO>* __restrict__ Xp, cpx<TO>* __restrict__ Yp,
                           const int* __restrict__ perm, const int* __restrict__ conjflag, int n,
                           int L) {
   const int64_t total = int64_t(n) * L;
@@ -58,6 +58,7 @@ __global__ void perm_in_t(const cpx<TI>* __restrict__ X, cpx<TO>* __restrict__ X
     const int p = int(e / L), k = int(e % L);
     cpx<TI> v = X[int64_t(k) * n + perm[p]];
     Xp[e] = {TO(v.re), conjflag[k] ? TO(-v.im) : TO(v.im)};
+    Yp[e] = {TO(0), TO(0)};
   }
 }
 
@@ -74,350 +75,272 @@ __global__ void perm_out_t(const cpx<TI>* __restrict__ Yp, cpx<TO>* __restrict__
   }
 }
 
-// Per-frequency product, one workgroup (4 waves) per block, all frequency
-// columns of a 64-column tile at once (lane = column).  Every slice element is
-// read once per tile.
-//   near block: Y_I[:, k] += sum_d f_d[k] D_d X_J[:, k]; X_J and D_d staged
-//               through LDS in 64 x 64 chunks, each wave owns 16 rows
-//   far block:  T = Vcat^H X_J (each wave 16 stacked columns, X_J staged
-//               through LDS), T[c][k] *= f_{d(c)}[k], Y_I += Ucat T
-// Accumulation into Yp with atomics.
+// ---- per-frequency product on the matrix cores ----------------------------------
+// Per far block (R stacked columns, Ubar m x R, Vbar n x R, column-major, the
+// block's stack contiguous): T = Vbar^H X_J, T' = F o T with F[c][k] = f_c[rep(k)],
+// Y_I += Ubar T'.  Per near block: Y_I += sum_d f_d[rep(k)] (D_d X_J)[:, k].
+//
+// Tiles of 16 rows by 16 frequency columns, four contraction values a step
+// (v_mfma_f32_16x16x4f32, v_mfma_f64_16x16x4f64: A[i][k] in lane i + 16 k, B[k][j] in
+// lane j + 16 k): leaves of 40 rows pad to 48, where 32-row tiles pad to 64, at the
+// same rate.  A wave multiplies two column tiles, so that an operator value
+// serves both.  Operator values are loaded a group of steps ahead; indices
+// beyond a block are clamped, against zeros on the other side of the product.
+//   near: a wave per (block, 16 rows, 16 CT columns), NEAR_XS steps of X_J in
+//     registers over the block's terms (X_J was re-read per term), wider blocks
+//     in several pieces.  CT = 1 where there are too few waves for the chip.
+//   far: a workgroup of four waves per (block, FC columns), T' of up to MM_CC
+//     stacked columns in LDS, larger stacks MM_CC at a time.
+// The workgroups of one block's column chunks have numbers 8 apart, so that they
+// run on one XCD and share the block in its L2.  Bound by the matrix cores and,
+// on small partitions, by latency.  5120-triangle sphere, 64 frequencies: 0.97 ms
+// in complex64 (1.36 with 32-row tiles, one workgroup a block), 1.4 ms in
+// complex128 (8.6 on the vector units).  Accumulation into Yp with atomics.
+typedef float mm_f4 __attribute__((ext_vector_type(4)));
+typedef double mm_d4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ mm_f4 mm(float a, float b, mm_f4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ mm_d4 mm(double a, double b, mm_d4 c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+
 template <typename T>
-__global__ void __launch_bounds__(256) perfreq_tiled(
-    const int* __restrict__ blk, const int* __restrict__ order, int nmv,
-    const int* __restrict__ bterm, const int64_t* __restrict__ toff,
-    const int64_t* __restrict__ tfoff, const int64_t* __restrict__ cols,
-    const int* __restrict__ bcol, const cpx<T>* __restrict__ pool, const int* __restrict__ colpos,
-    int L, const cpx<T>* __restrict__ Xp, cpx<T>* __restrict__ Yp) {
-  __shared__ cpx<T> xs[64 * 64];
-  __shared__ cpx<T> ds[64 * 64];
-  const int lane = threadIdx.x & 63;
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const cpx<T> zero = {T(0), T(0)};
-  for (int ob = blockIdx.x; ob < nmv; ob += gridDim.x) {
-    const int b = order[ob];
-    const int rb = blk[5 * b], m = blk[5 * b + 1] - rb, cb = blk[5 * b + 2],
-              n = blk[5 * b + 3] - cb;
-    const bool adm = blk[5 * b + 4] & 1;
-    for (int k0 = 0; k0 < L; k0 += 64) {
-      const int k = k0 + lane;
-      const bool kin = k < L;
-      const int kp = kin ? colpos[k] : 0;
-      if (!adm) {
-        for (int i0 = 0; i0 < m; i0 += 64) {
-          const int in = min(64, m - i0);
-          cpx<T> acc[16];
+struct Mm;
+template <>
+struct Mm<float> {
+  static constexpr int NEAR_XS = 16;   // steps of X_J held: 64 columns
+  static constexpr int FC = 64;        // far: frequency columns of a workgroup
+  // complex accumulator in Gauss's three products: k1 += (a_r + a_i) b_r,
+  // k2 += a_r (b_i - b_r), k3 += a_i (b_r + b_i); Re = k1 - k3, Im = k1 + k2
+  mm_f4 k1 = {0.f, 0.f, 0.f, 0.f}, k2 = k1, k3 = k1;
+  __device__ __forceinline__ void step(cpx<float> a, cpx<float> b) {
+    k1 = mm(a.re + a.im, b.re, k1);
+    k2 = mm(a.re, b.im - b.re, k2);
+    k3 = mm(a.im, b.re + b.im, k3);
+  }
+  __device__ __forceinline__ cpx<float> get(int r) const { return {k1[r] - k3[r], k1[r] + k2[r]}; }
+  static __device__ __forceinline__ int row(int r, int q) { return 4 * q + r; }   // of element r, lane group q
+};
+template <>
+struct Mm<double> {
+  static constexpr int NEAR_XS = 10;
+  static constexpr int FC = 32;
+  mm_d4 re = {0.0, 0.0, 0.0, 0.0}, im = re;
+  __device__ __forceinline__ void step(cpx<double> a, cpx<double> b) {
+    re = mm(a.re, b.re, re);
+    im = mm(a.re, b.im, im);
+    re = mm(-a.im, b.im, re);
+    im = mm(a.im, b.re, im);
+  }
+  __device__ __forceinline__ cpx<double> get(int r) const { return {re[r], im[r]}; }
+  static __device__ __forceinline__ int row(int r, int q) { return 4 * r + q; }
+};
+
+constexpr int MM_CC = 128;   // stacked columns of T' in LDS
+constexpr int MM_KU = 4;     // steps whose operator values are loaded together
+
+template <typename T>
+__device__ __forceinline__ void add_rows(cpx<T>* __restrict__ Yp, int rb, int m, int i0, int q, int L, int k,
+                                         const cpx<T> (&v)[4]) {
 #pragma unroll
-          for (int q = 0; q < 16; ++q) acc[q] = zero;
-          for (int j0 = 0; j0 < n; j0 += 64) {
-            const int jn = min(64, n - j0);
-            __syncthreads();
-            for (int e = threadIdx.x; e < jn * 64; e += 256) {
-              const int jj = e >> 6, kk = e & 63;
-              xs[e] = (k0 + kk < L) ? Xp[int64_t(cb + j0 + jj) * L + k0 + kk] : zero;
-            }
-            for (int d = bterm[b]; d < bterm[b + 1]; ++d) {
-              const cpx<T>* D = pool + toff[d];
-              __syncthreads();
-              for (int e = threadIdx.x; e < jn * 64; e += 256) {
-                const int jj = e >> 6, ii = e & 63;
-                ds[e] = ii < in ? D[int64_t(j0 + jj) * m + i0 + ii] : zero;
-              }
-              __syncthreads();
-              const cpx<T> f = kin ? pool[tfoff[d] + kp] : zero;
-              cpx<T> sacc[16];
-#pragma unroll
-              for (int q = 0; q < 16; ++q) sacc[q] = zero;
-              for (int jj = 0; jj < jn; ++jj) {
-                const cpx<T> x = xs[jj * 64 + lane];
-#pragma unroll
-                for (int q = 0; q < 16; ++q) {
-                  const cpx<T> dv = ds[jj * 64 + w * 16 + q];
-                  sacc[q].re += dv.re * x.re - dv.im * x.im;
-                  sacc[q].im += dv.re * x.im + dv.im * x.re;
-                }
-              }
-#pragma unroll
-              for (int q = 0; q < 16; ++q) {
-                acc[q].re += f.re * sacc[q].re - f.im * sacc[q].im;
-                acc[q].im += f.re * sacc[q].im + f.im * sacc[q].re;
-              }
-            }
-          }
-          if (kin) {
-#pragma unroll
-            for (int q = 0; q < 16; ++q) {
-              const int i = w * 16 + q;
-              if (i < in) {
-                cpx<T>* y = Yp + int64_t(rb + i0 + i) * L + k;
-                atomicAdd(&y->re, acc[q].re);
-                atomicAdd(&y->im, acc[q].im);
-              }
-            }
-          }
-        }
-      } else {
-        const int c0 = bcol[b], c1 = bcol[b + 1];
-        for (int cc = c0; cc < c1; cc += 64) {
-          const int cn = min(64, c1 - cc);
-          cpx<T> acc[16];
-#pragma unroll
-          for (int q = 0; q < 16; ++q) acc[q] = zero;
-          for (int j0 = 0; j0 < n; j0 += 64) {
-            const int jn = min(64, n - j0);
-            __syncthreads();
-            // X chunk into xs, the chunk of the stacked V columns into ds
-            for (int e = threadIdx.x; e < jn * 64; e += 256) {
-              const int jj = e >> 6, kk = e & 63;
-              xs[e] = (k0 + kk < L) ? Xp[int64_t(cb + j0 + jj) * L + k0 + kk] : zero;
-            }
-            for (int e = threadIdx.x; e < cn * 64; e += 256) {
-              const int cl = e >> 6, jj = e & 63;
-              ds[e] = jj < jn ? pool[cols[3 * (cc + cl) + 1] + j0 + jj] : zero;
-            }
-            __syncthreads();
-            for (int jj = 0; jj < jn; ++jj) {
-              const cpx<T> x = xs[jj * 64 + lane];
-#pragma unroll
-              for (int q = 0; q < 16; ++q) {
-                const cpx<T> v = ds[(w * 16 + q) * 64 + jj];
-                acc[q].re += v.re * x.re + v.im * x.im;   // conj(v) x
-                acc[q].im += v.re * x.im - v.im * x.re;
-              }
-            }
-          }
-          // scale by the fibers; T into ds
-          __syncthreads();
-#pragma unroll
-          for (int q = 0; q < 16; ++q) {
-            const int cl = w * 16 + q;
-            cpx<T> t = zero;
-            if (cl < cn && kin) {
-              const cpx<T> f = pool[cols[3 * (cc + cl) + 2] + kp];
-              t = {f.re * acc[q].re - f.im * acc[q].im, f.re * acc[q].im + f.im * acc[q].re};
-            }
-            ds[cl * 64 + lane] = t;
-          }
-          // Y_I += Ucat T: 64 rows at a time, U chunk staged into xs, 16 rows per wave
-          for (int ib0 = 0; ib0 < m; ib0 += 64) {
-            const int rn = min(64, m - ib0);
-            __syncthreads();
-            for (int e = threadIdx.x; e < cn * 64; e += 256) {
-              const int cl = e >> 6, r = e & 63;
-              xs[e] = r < rn ? pool[cols[3 * (cc + cl)] + ib0 + r] : zero;
-            }
-            __syncthreads();
-            cpx<T> yacc[16];
-#pragma unroll
-            for (int q = 0; q < 16; ++q) yacc[q] = zero;
-            for (int cl = 0; cl < cn; ++cl) {
-              const cpx<T> t = ds[cl * 64 + lane];
-#pragma unroll
-              for (int q = 0; q < 16; ++q) {
-                const cpx<T> u = xs[cl * 64 + w * 16 + q];
-                yacc[q].re += u.re * t.re - u.im * t.im;
-                yacc[q].im += u.re * t.im + u.im * t.re;
-              }
-            }
-            if (kin) {
-#pragma unroll
-              for (int q = 0; q < 16; ++q) {
-                const int r = w * 16 + q;
-                if (r < rn) {
-                  cpx<T>* y = Yp + int64_t(rb + ib0 + r) * L + k;
-                  atomicAdd(&y->re, yacc[q].re);
-                  atomicAdd(&y->im, yacc[q].im);
-                }
-              }
-            }
-          }
-        }
-      }
+  for (int r = 0; r < 4; ++r) {
+    const int i = i0 + Mm<T>::row(r, q);
+    if (i < m) {
+      cpx<T>* y = Yp + int64_t(rb + i) * L + k;
+      atomicAdd(&y->re, v[r].re);
+      atomicAdd(&y->im, v[r].im);
     }
   }
 }
 
-// ---- complex64 product on the matrix cores ------------------------------------
-// Per far block (R stacked columns, Ubar m x R, Vbar n x R, column-major, the
-// block's stack contiguous) and chunk of 64 frequency columns k:
-//   T = Vbar^H X_J (R x 64), T' = F o T with F[c][k] = f_c[rep(k)],
-//   Y_I += Ubar T'.
-// Per near block: Y_I += sum_d f_d[rep(k)] (D_d X_J)[:, k].
-// Complex products as three real v_mfma_f32_32x32x2f32 (Gauss's form; A[i][k] in lane
-// i + 32 k, B[k][j] in lane j + 32 k, D[8 (r / 4) + 4 (l / 32) + r % 4][l % 32]
-// in element r of lane l).  One workgroup of 4 waves per block; T' of up to
-// 128 stacked columns is held in LDS, larger stacks go 128 columns at a time.
-typedef float mf_v16 __attribute__((ext_vector_type(16)));
-
-__device__ __forceinline__ mf_v16 mf_zero() {
-  mf_v16 z;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) z[r] = 0.f;
-  return z;
-}
-__device__ __forceinline__ mf_v16 mfma32(float a, float b, mf_v16 c) {
-  return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
-}
-
-// one step of a complex product A B accumulated with three real products
-// (Gauss): k1 += (a_r + a_i) b_r, k2 += a_r (b_i - b_r), k3 += a_i (b_r + b_i);
-// then Re = k1 - k3, Im = k1 + k2
-__device__ __forceinline__ void gauss3(cpx<float> a, cpx<float> b, mf_v16& k1, mf_v16& k2, mf_v16& k3) {
-  k1 = mfma32(a.re + a.im, b.re, k1);
-  k2 = mfma32(a.re, b.im - b.re, k2);
-  k3 = mfma32(a.im, b.re + b.im, k3);
-}
-
-constexpr int MV_CC = 128;   // stacked columns per LDS chunk of T'
-constexpr int MV_KU = 8;     // MFMA steps whose operands are loaded ahead
-
-__global__ void __launch_bounds__(256) perfreq_mfma(
-    const int* __restrict__ blk, const int* __restrict__ order, int nmv,
-    const int* __restrict__ bterm, const int64_t* __restrict__ toff,
-    const int64_t* __restrict__ tfoff, const int64_t* __restrict__ cols,
-    const int* __restrict__ bcol, const cpx<float>* __restrict__ pool,
-    const int* __restrict__ colpos, int L, const cpx<float>* __restrict__ Xp,
-    cpx<float>* __restrict__ Yp) {
-  __shared__ cpx<float> Ts[MV_CC * 64];
-  const int lane = threadIdx.x & 63;
+// far: workgroups [0, wfar), near: the others, a task (block, row tile, column
+// chunk) per wave
+template <typename T, int CT>
+__global__ void __launch_bounds__(256, 2) perfreq_mm(
+    const int* __restrict__ blk, const int* __restrict__ farlist, int nfar, int wfar,
+    const int2* __restrict__ neartask, int nnear, const int* __restrict__ bterm, const int64_t* __restrict__ toff,
+    const int64_t* __restrict__ tfoff, const int64_t* __restrict__ cols, const int* __restrict__ bcol,
+    const cpx<T>* __restrict__ pool, const int* __restrict__ colpos, int L, const cpx<T>* __restrict__ Xp,
+    cpx<T>* __restrict__ Yp) {
+  constexpr int FC = Mm<T>::FC, TS = FC + 8;   // (row stride of T': the four rows a read touches in other banks)
+  __shared__ cpx<T> Ts[MM_CC * TS];
+  const int lane = threadIdx.x & 63, l16 = lane & 15, q = lane >> 4;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int lr = lane & 31, lh = lane >> 5;   // MFMA operand row / k-half
-  for (int ob = blockIdx.x; ob < nmv; ob += gridDim.x) {
-    const int b = order[ob];
-    const int rb = blk[5 * b], m = blk[5 * b + 1] - rb, cb = blk[5 * b + 2],
-              n = blk[5 * b + 3] - cb;
-    const bool adm = blk[5 * b + 4] & 1;
-    const int mt = (m + 31) >> 5;
-    for (int kc = 0; kc < L; kc += 64) {
-      if (!adm) {
-        // near block: every wave owns output tiles (row tile, k tile)
-        const int d0 = bterm[b], d1 = bterm[b + 1];
-        for (int tile = w; tile < mt * 2; tile += 4) {
-          const int it = tile >> 1, kt = tile & 1;
-          const int kcol = kc + kt * 32 + lr;
-          const bool kin = kcol < L;
-          const int kp = kin ? colpos[kcol] : 0;
-          const int ia = it * 32 + lr;   // A row of this lane
-          mf_v16 yr = mf_zero(), yi = mf_zero();
-          for (int d = d0; d < d1; ++d) {
-            const cpx<float>* D = pool + toff[d];
-            mf_v16 k1 = mf_zero(), k2 = mf_zero(), k3 = mf_zero();
-            for (int j0 = 0; j0 < n; j0 += 2 * MV_KU) {
-              // operands of MV_KU steps first, then their products
-              cpx<float> a[MV_KU], x[MV_KU];
+  const cpx<T> zero = {T(0), T(0)};
+  if (int(blockIdx.x) >= wfar) {
+    constexpr int XS = Mm<T>::NEAR_XS;
+    // task numbers: column chunks of four tasks 8 workgroups apart
+    const int nkc = (L + 16 * CT - 1) / (16 * CT);
+    const int id = blockIdx.x - wfar, loc = id >> 3;
+    const int ti = ((loc / nkc) * 8 + (id & 7)) * 4 + w, k0 = (loc % nkc) * 16 * CT;
+    if (ti >= nnear) return;
+    const int2 task = neartask[ti];
+    const int b = task.x, i0 = task.y;
+    const int rb = blk[5 * b], m = blk[5 * b + 1] - rb, cb = blk[5 * b + 2], n = blk[5 * b + 3] - cb;
+    const int d0 = bterm[b], d1 = bterm[b + 1];
+    const int ia = min(i0 + l16, m - 1);
+    bool kin[CT];
+    int kp[CT];
 #pragma unroll
-              for (int u = 0; u < MV_KU; ++u) {
-                const int j = j0 + 2 * u + lh;
-                a[u] = (ia < m && j < n) ? D[int64_t(j) * m + ia] : cpx<float>{0.f, 0.f};
-                x[u] = (kin && j < n) ? Xp[int64_t(cb + j) * L + kcol] : cpx<float>{0.f, 0.f};
-              }
+    for (int u = 0; u < CT; ++u) {
+      kin[u] = k0 + 16 * u + l16 < L;
+      kp[u] = kin[u] ? colpos[k0 + 16 * u + l16] : 0;
+    }
+    cpx<T> y[CT][4];
 #pragma unroll
-              for (int u = 0; u < MV_KU; ++u) gauss3(a[u], x[u], k1, k2, k3);
-            }
-            const cpx<float> f = kin ? pool[tfoff[d] + kp] : cpx<float>{0.f, 0.f};
+    for (int u = 0; u < CT; ++u)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              const float pr = k1[r] - k3[r], pi = k1[r] + k2[r];
-              yr[r] += f.re * pr - f.im * pi;
-              yi[r] += f.re * pi + f.im * pr;
-            }
+      for (int r = 0; r < 4; ++r) y[u][r] = zero;
+    for (int j0 = 0; j0 < n; j0 += 4 * XS) {
+      const int jn = min(4 * XS, n - j0);
+      cpx<T> x[XS][CT];
+#pragma unroll
+      for (int s = 0; s < XS; ++s)
+#pragma unroll
+        for (int u = 0; u < CT; ++u) {
+          const int j = 4 * s + q;
+          x[s][u] = (j < jn && kin[u]) ? Xp[int64_t(cb + j0 + j) * L + k0 + 16 * u + l16] : zero;
+        }
+      const cpx<T>* D = pool + toff[d0] + int64_t(j0) * m + ia;
+      cpx<T> a[MM_KU];
+#pragma unroll
+      for (int v = 0; v < MM_KU; ++v) a[v] = D[min(4 * v + q, jn - 1) * m];
+      for (int d = d0; d < d1; ++d) {
+        const cpx<T>* Dn = d + 1 < d1 ? pool + toff[d + 1] + int64_t(j0) * m + ia : D;
+        cpx<T> f[CT];
+#pragma unroll
+        for (int u = 0; u < CT; ++u) f[u] = pool[tfoff[d] + kp[u]];
+        Mm<T> t[CT];
+#pragma unroll
+        for (int s0 = 0; s0 < XS; s0 += MM_KU) {
+          if (4 * s0 >= jn) break;
+          const bool last = 4 * (s0 + MM_KU) >= jn;
+          const cpx<T>* P = last ? Dn : D;
+          const int jb = last ? 0 : 4 * (s0 + MM_KU);
+          cpx<T> c[MM_KU];
+#pragma unroll
+          for (int v = 0; v < MM_KU; ++v) {
+            c[v] = a[v];
+            a[v] = P[min(jb + 4 * v + q, jn - 1) * m];
           }
-          if (kin) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              const int row = it * 32 + 8 * (r >> 2) + 4 * lh + (r & 3);
-              if (row < m) {
-                cpx<float>* y = Yp + int64_t(rb + row) * L + kcol;
-                atomicAdd(&y->re, yr[r]);
-                atomicAdd(&y->im, yi[r]);
-              }
-            }
+          for (int v = 0; v < MM_KU; ++v) {
+            if (s0 + v >= XS) break;
+#pragma unroll
+            for (int u = 0; u < CT; ++u) t[u].step(c[v], x[s0 + v][u]);
           }
         }
-        continue;
+        D = Dn;
+#pragma unroll
+        for (int u = 0; u < CT; ++u)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const cpx<T> p = cmul(f[u], t[u].get(r));
+            y[u][r].re += p.re;
+            y[u][r].im += p.im;
+          }
       }
-      const int c0b = bcol[b], R = bcol[b + 1] - c0b;
-      if (R == 0) continue;
-      const cpx<float>* Ust = pool + cols[3 * c0b];
-      const cpx<float>* Vst = pool + cols[3 * c0b + 1];
-      for (int cc = 0; cc < R; cc += MV_CC) {
-        const int cn = min(MV_CC, R - cc);
-        const int ct = (cn + 31) >> 5;
-        __syncthreads();   // Ts free
-        // T' = F o (Vbar^H X_J) for stacked columns cc .. cc + cn
-        for (int tile = w; tile < ct * 2; tile += 4) {
-          const int ti = tile >> 1, kt = tile & 1;
-          const int kcol = kc + kt * 32 + lr;
-          const bool kin = kcol < L;
-          const int ca = cc + ti * 32 + lr;   // A row (stacked column) of this lane
-          const cpx<float>* Vc = Vst + int64_t(ca) * n;
-          mf_v16 k1 = mf_zero(), k2 = mf_zero(), k3 = mf_zero();
-          for (int j0 = 0; j0 < n; j0 += 2 * MV_KU) {
-            cpx<float> v[MV_KU], x[MV_KU];
+    }
 #pragma unroll
-            for (int u = 0; u < MV_KU; ++u) {
-              const int j = j0 + 2 * u + lh;
-              const cpx<float> vv = (ca < R && j < n) ? Vc[j] : cpx<float>{0.f, 0.f};
-              v[u] = {vv.re, -vv.im};   // conj(v)
-              x[u] = (kin && j < n) ? Xp[int64_t(cb + j) * L + kcol] : cpx<float>{0.f, 0.f};
-            }
+    for (int u = 0; u < CT; ++u)
+      if (kin[u]) add_rows<T>(Yp, rb, m, i0, q, L, k0 + 16 * u + l16, y[u]);
+    return;
+  }
+  const int nkc = (L + FC - 1) / FC;
+  const int loc = blockIdx.x >> 3, fi = (loc / nkc) * 8 + (blockIdx.x & 7), kc = (loc % nkc) * FC;
+  if (fi >= nfar) return;
+  const int b = farlist[fi];
+  const int rb = blk[5 * b], m = blk[5 * b + 1] - rb, cb = blk[5 * b + 2], n = blk[5 * b + 3] - cb;
+  const int c0b = bcol[b], R = bcol[b + 1] - c0b;
+  if (R == 0) return;
+  const cpx<T>* Ust = pool + cols[3 * c0b];
+  const cpx<T>* Vst = pool + cols[3 * c0b + 1];
+  const int halves = min(FC, L - kc) > 32 ? 2 : 1;   // 32-column halves that hold a column
+  for (int cc = 0; cc < R; cc += MM_CC) {
+    const int cn = min(MM_CC, R - cc), ct = (cn + 15) >> 4;
+    if (cc > 0) __syncthreads();   // the last chunk's T' is read
+    // T' = F o (Vbar^H X_J) for stacked columns cc .. cc + cn
+    for (int tile = w; tile < ct * halves; tile += 4) {
+      const int ti = tile / halves, kb = kc + (tile % halves) * 32;
+      bool kin[2];
+      const cpx<T>* xk[2];
 #pragma unroll
-            for (int u = 0; u < MV_KU; ++u) gauss3(v[u], x[u], k1, k2, k3);
-          }
-          mf_v16 tr, tim;
+      for (int u = 0; u < 2; ++u) {
+        kin[u] = kb + 16 * u + l16 < L;
+        xk[u] = Xp + int64_t(cb) * L + (kin[u] ? kb + 16 * u + l16 : 0);
+      }
+      const cpx<T>* Vc = Vst + int64_t(min(cc + ti * 16 + l16, R - 1)) * n;
+      Mm<T> t[2];
+      cpx<T> a[MM_KU], x[MM_KU][2];
+      auto load = [&](int j0) {
 #pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            tr[r] = k1[r] - k3[r];
-            tim[r] = k1[r] + k2[r];
-          }
-          const int kp = kin ? colpos[kcol] : 0;
+        for (int v = 0; v < MM_KU; ++v) {
+          const int j = j0 + 4 * v + q, jc = min(j, n - 1);
+          a[v] = Vc[jc];
 #pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int cl = ti * 32 + 8 * (r >> 2) + 4 * lh + (r & 3);   // local stacked column
-            cpx<float> t = {0.f, 0.f};
-            if (cl < cn && kin) {
-              const cpx<float> f = pool[cols[3 * (c0b + cc + cl) + 2] + kp];
-              t = {f.re * tr[r] - f.im * tim[r], f.re * tim[r] + f.im * tr[r]};
-            }
-            Ts[cl * 64 + kt * 32 + lr] = t;
+          for (int u = 0; u < 2; ++u) {
+            const cpx<T> xx = xk[u][int64_t(jc) * L];
+            x[v][u] = (j < n && kin[u]) ? xx : zero;
           }
         }
-        __syncthreads();
-        // Y_I += Ubar[:, cc .. cc + cn] T'
-        for (int tile = w; tile < mt * 2; tile += 4) {
-          const int it = tile >> 1, kt = tile & 1;
-          const int kcol = kc + kt * 32 + lr;
-          const int ia = it * 32 + lr;
-          mf_v16 k1 = mf_zero(), k2 = mf_zero(), k3 = mf_zero();
-          for (int c2 = 0; c2 < ct * 32; c2 += 2 * MV_KU) {
-            cpx<float> uu[MV_KU], tt[MV_KU];
+      };
+      load(0);
+      for (int j0 = 0; j0 < n; j0 += 4 * MM_KU) {
+        cpx<T> c[MM_KU], xc[MM_KU][2];
 #pragma unroll
-            for (int q = 0; q < MV_KU; ++q) {
-              const int cl = c2 + 2 * q + lh;   // < ct * 32 (ct * 32 is a multiple of 2 MV_KU)
-              uu[q] = (ia < m && cl < cn) ? Ust[int64_t(cc + cl) * m + ia] : cpx<float>{0.f, 0.f};
-              tt[q] = Ts[cl * 64 + kt * 32 + lr];
-            }
-#pragma unroll
-            for (int q = 0; q < MV_KU; ++q) gauss3(uu[q], tt[q], k1, k2, k3);
-          }
-          mf_v16 yr, yi;
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            yr[r] = k1[r] - k3[r];
-            yi[r] = k1[r] + k2[r];
-          }
-          if (kcol < L) {
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              const int row = it * 32 + 8 * (r >> 2) + 4 * lh + (r & 3);
-              if (row < m) {
-                cpx<float>* y = Yp + int64_t(rb + row) * L + kcol;
-                atomicAdd(&y->re, yr[r]);
-                atomicAdd(&y->im, yi[r]);
-              }
-            }
-          }
+        for (int v = 0; v < MM_KU; ++v) {
+          c[v] = {a[v].re, -a[v].im};   // conj(v)
+          xc[v][0] = x[v][0];
+          xc[v][1] = x[v][1];
         }
+        if (j0 + 4 * MM_KU < n) load(j0 + 4 * MM_KU);
+#pragma unroll
+        for (int v = 0; v < MM_KU; ++v)
+#pragma unroll
+          for (int u = 0; u < 2; ++u) t[u].step(c[v], xc[v][u]);
+      }
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int kp = kin[u] ? colpos[kb + 16 * u + l16] : 0;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int cl = ti * 16 + Mm<T>::row(r, q);   // local stacked column
+          cpx<T> v = zero;
+          if (cl < cn && kin[u]) v = cmul(pool[cols[3 * (c0b + cc + cl) + 2] + kp], t[u].get(r));
+          Ts[cl * TS + kb - kc + 16 * u + l16] = v;
+        }
+      }
+    }
+    __syncthreads();
+    // Y_I += Ubar[:, cc .. cc + cn] T'
+    const int mt = (m + 15) >> 4;
+    for (int tile = w; tile < mt * halves; tile += 4) {
+      const int i0 = (tile / halves) * 16, kb = kc + (tile % halves) * 32;
+      const cpx<T>* Ui = Ust + int64_t(cc) * m + min(i0 + l16, m - 1);
+      Mm<T> t[2];
+      cpx<T> a[MM_KU];
+#pragma unroll
+      for (int v = 0; v < MM_KU; ++v) a[v] = Ui[int64_t(min(4 * v + q, cn - 1)) * m];
+      for (int c2 = 0; c2 < cn; c2 += 4 * MM_KU) {
+        cpx<T> c[MM_KU];
+#pragma unroll
+        for (int v = 0; v < MM_KU; ++v) {
+          c[v] = a[v];
+          a[v] = Ui[int64_t(min(c2 + 4 * MM_KU + 4 * v + q, cn - 1)) * m];
+        }
+#pragma unroll
+        for (int v = 0; v < MM_KU; ++v)
+#pragma unroll
+          for (int u = 0; u < 2; ++u)
+            t[u].step(c[v], Ts[(c2 + 4 * v + q) * TS + kb - kc + 16 * u + l16]);   // rows < 16 ct
+      }
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int k = kb + 16 * u + l16;
+        const cpx<T> v[4] = {t[u].get(0), t[u].get(1), t[u].get(2), t[u].get(3)};
+        if (k < L) add_rows<T>(Yp, rb, m, i0, q, L, k, v);
       }
     }
   }
@@ -599,28 +522,29 @@ static void enqueue_perfreq(gcq_context* ctx, hipStream_t st, int precision, con
   const int* d_colpos = F.pmeta.as<int>();
   const int* d_conj = d_colpos + L;
   const int* perm = ctx->d_perm.as<int>();
-  const int g = 4096;
+  const int g = int(std::min<int64_t>((nl + 255) / 256, 4096));
   if (precision == GCQ_C128)
-    hipLaunchKernelGGL((perm_in_t<double, T>), dim3(g), dim3(256), 0, st, (const cpx<double>*)X, Xp,
+    hipLaunchKernelGGL((perm_in_t<double, T>), dim3(g), dim3(256), 0, st, (const cpx<double>*)X, Xp, Yp,
                        perm, d_conj, n, L);
   else
-    hipLaunchKernelGGL((perm_in_t<float, T>), dim3(g), dim3(256), 0, st, (const cpx<float>*)X, Xp,
+    hipLaunchKernelGGL((perm_in_t<float, T>), dim3(g), dim3(256), 0, st, (const cpx<float>*)X, Xp, Yp,
                        perm, d_conj, n, L);
-  hipLaunchKernelGGL(zero3<T>, dim3(g), dim3(256), 0, st, Yp, nl);
-  const int cus = ctx->cus;
-  if constexpr (std::is_same<T, float>::value) {
-    hipLaunchKernelGGL(perfreq_mfma, dim3(std::max(1, std::min(F.n_mvblocks, cus * 4))), dim3(256), 0,
-                       st, ctx->d_blk.as<int>(), F.d_mvorder.as<int>(), F.n_mvblocks,
-                       F.d_bterm.as<int>(), F.d_toff.as<int64_t>(), F.d_tfoff.as<int64_t>(),
-                       F.d_cols.as<int64_t>(), F.d_bcol.as<int>(), F.slices.as<cpx<float>>(), d_colpos,
-                       L, Xp, Yp);
-  } else {
-    hipLaunchKernelGGL(perfreq_tiled<T>, dim3(std::max(1, std::min(F.n_mvblocks, cus * 2))), dim3(256),
-                       0, st, ctx->d_blk.as<int>(), F.d_mvorder.as<int>(), F.n_mvblocks,
-                       F.d_bterm.as<int>(), F.d_toff.as<int64_t>(), F.d_tfoff.as<int64_t>(),
-                       F.d_cols.as<int64_t>(), F.d_bcol.as<int>(), F.slices.as<cpx<T>>(), d_colpos, L,
-                       Xp, Yp);
-  }
+  // two column tiles a wave, one where the near blocks would not give every SIMD
+  // two waves
+  auto go = [&](auto ct) {
+    constexpr int CT = decltype(ct)::value;
+    const int kf = (L + Mm<T>::FC - 1) / Mm<T>::FC, kn = (L + 16 * CT - 1) / (16 * CT);
+    const int wfar = (F.n_far + 7) / 8 * 8 * kf, wnear = (F.n_neartask + 31) / 32 * 8 * kn;
+    if (wfar + wnear > 0)
+      hipLaunchKernelGGL((perfreq_mm<T, CT>), dim3(wfar + wnear), dim3(256), 0, st, ctx->d_blk.as<int>(),
+                         F.d_farlist.as<int>(), F.n_far, wfar, F.d_neartask.as<int2>(), F.n_neartask,
+                         F.d_bterm.as<int>(), F.d_toff.as<int64_t>(), F.d_tfoff.as<int64_t>(),
+                         F.d_cols.as<int64_t>(), F.d_bcol.as<int>(), F.slices.as<cpx<T>>(), d_colpos, L, Xp, Yp);
+  };
+  if (int64_t(F.n_neartask) * ((L + 31) / 32) < int64_t(ctx->cus) * 8)
+    go(std::integral_constant<int, 1>());
+  else
+    go(std::integral_constant<int, 2>());
   if (precision == GCQ_C128)
     hipLaunchKernelGGL((perm_out_t<T, double>), dim3(g), dim3(256), 0, st, Yp, (cpx<double>*)Y, perm,
                        d_conj, n, L);
