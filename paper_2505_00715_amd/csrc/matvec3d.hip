@@ -84,8 +84,8 @@ __global__ void perm_out_t(const cpx<TI>* __restrict__ Yp, cpx<TO>* __restrict__
 // (v_mfma_f32_16x16x4f32, v_mfma_f64_16x16x4f64: A[i][k] in lane i + 16 k, B[k][j] in
 // lane j + 16 k): leaves of 40 rows pad to 48, where 32-row tiles pad to 64, at the
 // same rate.  A wave multiplies two column tiles, so that an operator value
-// serves both.  Operator values are loaded a group of steps ahead; indices
-// beyond a block are clamped, against zeros on the other side of the product.
+// serves both.  Operator values are loaded a term (near) or KU steps
+// (far) ahead, which memory latency takes at two waves a SIMD; indices beyond a block are clamped, against zeros on the other side of the product.
 //   near: a wave per (block, 16 rows, 16 CT columns), NEAR_XS steps of X_J in
 //     registers over the block's terms (X_J was re-read per term), wider blocks
 //     in several pieces.  CT = 1 where there are too few waves for the chip.
@@ -93,7 +93,7 @@ __global__ void perm_out_t(const cpx<TI>* __restrict__ Yp, cpx<TO>* __restrict__
 //     stacked columns in LDS, larger stacks MM_CC at a time.
 // The workgroups of one block's column chunks have numbers 8 apart, so that they
 // run on one XCD and share the block in its L2.  Bound by the matrix cores and,
-// on small partitions, by latency.  5120-triangle sphere, 64 frequencies: 0.97 ms
+// on small partitions, by latency.  5120-triangle sphere, 64 frequencies: 0.90 ms
 // in complex64 (1.36 with 32-row tiles, one workgroup a block), 1.4 ms in
 // complex128 (8.6 on the vector units).  Accumulation into Yp with atomics.
 typedef float mm_f4 __attribute__((ext_vector_type(4)));
@@ -112,6 +112,7 @@ template <>
 struct Mm<float> {
   static constexpr int NEAR_XS = 16;   // steps of X_J held: 64 columns
   static constexpr int FC = 64;        // far: frequency columns of a workgroup
+  static constexpr int KU = 8;         // far: steps whose operands are loaded together, ahead of their products
   // complex accumulator in Gauss's three products: k1 += (a_r + a_i) b_r,
   // k2 += a_r (b_i - b_r), k3 += a_i (b_r + b_i); Re = k1 - k3, Im = k1 + k2
   mm_f4 k1 = {0.f, 0.f, 0.f, 0.f}, k2 = k1, k3 = k1;
@@ -127,6 +128,7 @@ template <>
 struct Mm<double> {
   static constexpr int NEAR_XS = 10;
   static constexpr int FC = 32;
+  static constexpr int KU = 4;
   mm_d4 re = {0.0, 0.0, 0.0, 0.0}, im = re;
   __device__ __forceinline__ void step(cpx<double> a, cpx<double> b) {
     re = mm(a.re, b.re, re);
@@ -139,7 +141,6 @@ struct Mm<double> {
 };
 
 constexpr int MM_CC = 128;   // stacked columns of T' in LDS
-constexpr int MM_KU = 4;     // steps whose operator values are loaded together
 
 template <typename T>
 __device__ __forceinline__ void add_rows(cpx<T>* __restrict__ Yp, int rb, int m, int i0, int q, int L, int k,
@@ -164,7 +165,7 @@ __global__ void __launch_bounds__(256, 2) perfreq_mm(
     const int64_t* __restrict__ tfoff, const int64_t* __restrict__ cols, const int* __restrict__ bcol,
     const cpx<T>* __restrict__ pool, const int* __restrict__ colpos, int L, const cpx<T>* __restrict__ Xp,
     cpx<T>* __restrict__ Yp) {
-  constexpr int FC = Mm<T>::FC, TS = FC + 8;   // (row stride of T': the four rows a read touches in other banks)
+  constexpr int FC = Mm<T>::FC, KU = Mm<T>::KU, TS = FC + 8;   // (row stride of T': the four rows a read touches in other banks)
   __shared__ cpx<T> Ts[MM_CC * TS];
   const int lane = threadIdx.x & 63, l16 = lane & 15, q = lane >> 4;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -203,10 +204,11 @@ __global__ void __launch_bounds__(256, 2) perfreq_mm(
           const int j = 4 * s + q;
           x[s][u] = (j < jn && kin[u]) ? Xp[int64_t(cb + j0 + j) * L + k0 + 16 * u + l16] : zero;
         }
+      // a[s]: step s of the current term, replaced by the next term's as it is used
       const cpx<T>* D = pool + toff[d0] + int64_t(j0) * m + ia;
-      cpx<T> a[MM_KU];
+      cpx<T> a[XS];
 #pragma unroll
-      for (int v = 0; v < MM_KU; ++v) a[v] = D[min(4 * v + q, jn - 1) * m];
+      for (int s = 0; s < XS; ++s) a[s] = D[min(4 * s + q, jn - 1) * m];
       for (int d = d0; d < d1; ++d) {
         const cpx<T>* Dn = d + 1 < d1 ? pool + toff[d + 1] + int64_t(j0) * m + ia : D;
         cpx<T> f[CT];
@@ -214,23 +216,12 @@ __global__ void __launch_bounds__(256, 2) perfreq_mm(
         for (int u = 0; u < CT; ++u) f[u] = pool[tfoff[d] + kp[u]];
         Mm<T> t[CT];
 #pragma unroll
-        for (int s0 = 0; s0 < XS; s0 += MM_KU) {
-          if (4 * s0 >= jn) break;
-          const bool last = 4 * (s0 + MM_KU) >= jn;
-          const cpx<T>* P = last ? Dn : D;
-          const int jb = last ? 0 : 4 * (s0 + MM_KU);
-          cpx<T> c[MM_KU];
+        for (int s = 0; s < XS; ++s) {
+          if (4 * s >= jn) break;
+          const cpx<T> c = a[s];
+          a[s] = Dn[min(4 * s + q, jn - 1) * m];
 #pragma unroll
-          for (int v = 0; v < MM_KU; ++v) {
-            c[v] = a[v];
-            a[v] = P[min(jb + 4 * v + q, jn - 1) * m];
-          }
-#pragma unroll
-          for (int v = 0; v < MM_KU; ++v) {
-            if (s0 + v >= XS) break;
-#pragma unroll
-            for (int u = 0; u < CT; ++u) t[u].step(c[v], x[s0 + v][u]);
-          }
+          for (int u = 0; u < CT; ++u) t[u].step(c, x[s][u]);
         }
         D = Dn;
 #pragma unroll
@@ -273,10 +264,10 @@ __global__ void __launch_bounds__(256, 2) perfreq_mm(
       }
       const cpx<T>* Vc = Vst + int64_t(min(cc + ti * 16 + l16, R - 1)) * n;
       Mm<T> t[2];
-      cpx<T> a[MM_KU], x[MM_KU][2];
+      cpx<T> a[KU], x[KU][2];
       auto load = [&](int j0) {
 #pragma unroll
-        for (int v = 0; v < MM_KU; ++v) {
+        for (int v = 0; v < KU; ++v) {
           const int j = j0 + 4 * v + q, jc = min(j, n - 1);
           a[v] = Vc[jc];
 #pragma unroll
@@ -287,17 +278,17 @@ __global__ void __launch_bounds__(256, 2) perfreq_mm(
         }
       };
       load(0);
-      for (int j0 = 0; j0 < n; j0 += 4 * MM_KU) {
-        cpx<T> c[MM_KU], xc[MM_KU][2];
+      for (int j0 = 0; j0 < n; j0 += 4 * KU) {
+        cpx<T> c[KU], xc[KU][2];
 #pragma unroll
-        for (int v = 0; v < MM_KU; ++v) {
+        for (int v = 0; v < KU; ++v) {
           c[v] = {a[v].re, -a[v].im};   // conj(v)
           xc[v][0] = x[v][0];
           xc[v][1] = x[v][1];
         }
-        if (j0 + 4 * MM_KU < n) load(j0 + 4 * MM_KU);
+        if (j0 + 4 * KU < n) load(j0 + 4 * KU);
 #pragma unroll
-        for (int v = 0; v < MM_KU; ++v)
+        for (int v = 0; v < KU; ++v)
 #pragma unroll
           for (int u = 0; u < 2; ++u) t[u].step(c[v], xc[v][u]);
       }
@@ -320,21 +311,21 @@ __global__ void __launch_bounds__(256, 2) perfreq_mm(
       const int i0 = (tile / halves) * 16, kb = kc + (tile % halves) * 32;
       const cpx<T>* Ui = Ust + int64_t(cc) * m + min(i0 + l16, m - 1);
       Mm<T> t[2];
-      cpx<T> a[MM_KU];
+      cpx<T> a[KU];
 #pragma unroll
-      for (int v = 0; v < MM_KU; ++v) a[v] = Ui[int64_t(min(4 * v + q, cn - 1)) * m];
-      for (int c2 = 0; c2 < cn; c2 += 4 * MM_KU) {
-        cpx<T> c[MM_KU];
+      for (int v = 0; v < KU; ++v) a[v] = Ui[int64_t(min(4 * v + q, cn - 1)) * m];
+      for (int c2 = 0; c2 < cn; c2 += 4 * KU) {
+        cpx<T> c[KU];
 #pragma unroll
-        for (int v = 0; v < MM_KU; ++v) {
+        for (int v = 0; v < KU; ++v) {
           c[v] = a[v];
-          a[v] = Ui[int64_t(min(c2 + 4 * MM_KU + 4 * v + q, cn - 1)) * m];
+          a[v] = Ui[int64_t(min(c2 + 4 * KU + 4 * v + q, cn - 1)) * m];
         }
 #pragma unroll
-        for (int v = 0; v < MM_KU; ++v)
+        for (int v = 0; v < KU; ++v)
 #pragma unroll
           for (int u = 0; u < 2; ++u)
-            t[u].step(c[v], Ts[(c2 + 4 * v + q) * TS + kb - kc + 16 * u + l16]);   // rows < 16 ct
+            if (c2 + 4 * v < 16 * ct) t[u].step(c[v], Ts[(c2 + 4 * v + q) * TS + kb - kc + 16 * u + l16]);
       }
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
