@@ -29,7 +29,7 @@ struct PlainEntry {
 // ALLFAR = false the others; each instance skips the pairs of the other kind.
 // NW waves work on one pair together; DLP: entries of the double layer.
 template <typename T, bool ALLFAR, int NW, bool DLP>
-__global__ void __launch_bounds__(NW * 64) aca_kernel(Tab tab, const PairDesc* __restrict__ pairs,
+__global__ void __launch_bounds__(NW * 64, NW == 1 && ALLFAR && sizeof(T) == 4 ? 4 : 1) aca_kernel(Tab tab, const PairDesc* __restrict__ pairs,
                                                       const int* __restrict__ order, int npairs,
                                                       unsigned char* __restrict__ ws, double tol,
                                                       int max_rank, int* __restrict__ out_rank,
@@ -86,9 +86,11 @@ static void launch_aca(bool dlp, int nw, int grid, hipStream_t st, Args... args)
 }
 
 // rank classes of the recompression: class c holds the pairs whose ACA rank k
-// lies in (RC_LO[c], RC_LO[c + 1]]
-constexpr int RC_N = 7;
-__constant__ int RC_LO[RC_N + 1] = {-1, 8, 12, 16, 18, 24, 32, 64};
+// lies in (RC_LO[c], RC_LO[c + 1]].  The class to 56 fills a compute unit's LDS
+// (150 KB) with eight waves on one pair: the few pairs above 32 end a launch, and
+// in global scratch one of them took about 3 ms.
+constexpr int RC_N = 8;
+__constant__ int RC_LO[RC_N + 1] = {-1, 8, 12, 16, 18, 24, 32, 56, 64};
 __device__ __forceinline__ int rank_class(int k) {
   int c = 0;
   while (c < RC_N - 1 && k > RC_LO[c + 1]) ++c;
@@ -173,9 +175,11 @@ static int launch_recompress(gcq_context* ctx, int nc, const PairDesc* pairs, un
   hipLaunchKernelGGL(recompress_classify, dim3(cg), dim3(256), 0, st, rank, nc, cls, list, 1);
   GCQ_HIP(hipEventRecord(ctx->evfork, st));
   for (int i = 0; i < 3; ++i) GCQ_HIP(hipStreamWaitEvent(ctx->side[i], ctx->evfork, 0));
-  const int g1 = std::min(nc, 5120), g2 = std::min(nc, 2560), g4 = std::min(nc, 1024);
+  const int g1 = std::min(nc, 5120), g2 = std::min(nc, 2560), g4 = std::min(nc, 1024), g8 = std::min(nc, 512);
   hipLaunchKernelGGL((recompress_kernel<T, 64, 4, true>), dim3(std::min(nc, RECOMP_GL_GRID)), dim3(256), 0,
-                     ctx->side[0], pairs, ws, rank, t, tol, rec, jws, 6, cls, list);
+                     ctx->side[0], pairs, ws, rank, t, tol, rec, jws, 7, cls, list);
+  hipLaunchKernelGGL((recompress_kernel<T, 56, 8, false>), dim3(g8), dim3(512), 0, ctx->side[0], pairs, ws,
+                     rank, t, tol, rec, jws, 6, cls, list);
   hipLaunchKernelGGL((recompress_kernel<T, 32, 4, false>), dim3(g4), dim3(256), 0, ctx->side[0], pairs, ws,
                      rank, t, tol, rec, jws, 5, cls, list);
   hipLaunchKernelGGL((recompress_kernel<T, 24, 2, false>), dim3(g2), dim3(128), 0, ctx->side[0], pairs, ws,
@@ -245,6 +249,21 @@ struct AcaRun {
   std::vector<int> slot;        // frequency slot per pair
 };
 
+// Whether a block's float entries are all below the smallest pivot at sigma, so
+// that its ACA would visit every row and end with rank 0: each entry is at most
+//   A / (4 pi r) exp(-Re sigma r)              (single layer)
+//   A (1 + |sigma| r) / (4 pi r^2) exp(-Re sigma r)   (double layer)
+// at the boxes' distance r (both fall with r where Re sigma r > 1), A the largest
+// panel area, and an entry below FLT_MIN is no pivot; a factor of 16 is left for
+// rounding.  High frequencies of a set leave half the pairs of a sphere in this
+// state, which took a third of the ACA kernel's time.
+static bool underflows(double dist, double area, std::complex<double> sigma, bool dlp) {
+  if (!(sigma.real() * dist > 1.0)) return false;
+  double lg = std::log2(area * INV4PI / dist) - sigma.real() * dist * 1.4426950408889634;
+  if (dlp) lg += std::log2((1.0 + std::abs(sigma) * dist) / dist);
+  return lg < -126.0 - 4.0;
+}
+
 template <typename T>
 static int run_aca_pairs(gcq_context* ctx, std::vector<PairDesc>& desc, std::vector<int>& order,
                          double tol, int max_rank, bool recompress, std::vector<int>& rank_aca,
@@ -253,10 +272,10 @@ static int run_aca_pairs(gcq_context* ctx, std::vector<PairDesc>& desc, std::vec
                          double& ms_aca, double& ms_rec, double& ms_apply, int64_t budget) {
   hipStream_t st = ctx->stream;
   const int np = int(desc.size());
-  rank_aca.assign(np, 0);
+  rank_aca.assign(np, 0);   // (pairs the order leaves out keep rank 0)
   rank_out.assign(np, 0);
-  status.assign(np, 0);
-  out_off.assign(np, -1);
+  status.assign(np, ST_EXACT);
+  out_off.assign(np, 0);
   const int dev_cus = ctx->cus;
   // chunks in work-list order, each within the workspace budget
   size_t pos = 0;
@@ -291,7 +310,7 @@ static int run_aca_pairs(gcq_context* ctx, std::vector<PairDesc>& desc, std::vec
     int* d_status = d_rank + nc;
     int* d_t = d_status + nc;
     int* d_counter = d_t + nc;
-    int* d_cls = d_counter + 8;      // rank classes of the recompression (3 x 7 counters)
+    int* d_cls = d_counter + 8;      // rank classes of the recompression (3 x 8 counters)
     int* d_list = d_counter + 32;    // the pairs class by class
     hipLaunchKernelGGL(zero_int, dim3(1), dim3(64), 0, st, d_counter, 32);
     int nnf = 0;
@@ -313,7 +332,7 @@ static int run_aca_pairs(gcq_context* ctx, std::vector<PairDesc>& desc, std::vec
     // the recompression follows on the device without a host round trip; the
     // split event divides the region between the two
     GCQ_HIP(hipEventRecord(ctx->evm, st));
-    // recompression by rank classes; matrices above 32 terms live in global scratch
+    // recompression by rank classes; matrices above 56 terms live in global scratch
     GCQ_TRY(launch_recompress<T>(ctx, nc, ctx->scratchB.as<PairDesc>(), ctx->scratchA.as<unsigned char>(), d_rank,
                                  d_t, tol, recompress ? 1 : 0, ctx->scratchD.as<unsigned char>(), d_cls, d_list));
     GCQ_HIP(hipGetLastError());
@@ -518,6 +537,27 @@ GCQ_API int gcq_aca_blocks(gcq_context* ctx, const int32_t* freq_idx, int32_t n_
       d.ws = 0;
     }
   }
+  // pairs whose entries all underflow have rank 0 and are not launched
+  std::vector<char> zero_pair(desc.size(), 0);
+  if (precision == GCQ_C64) {
+    double area = 0.0;
+    for (double a : ctx->area) area = std::max(area, a);
+    std::vector<double> dist(nfar);
+    for (int f = 0; f < nfar; ++f) {
+      const Block& B = ctx->blocks[ctx->far_ids[f]];
+      const Cluster& A = ctx->clusters[B.row];
+      const Cluster& C = ctx->clusters[B.col];
+      double d2 = 0.0;
+      for (int k = 0; k < 3; ++k) {
+        const double gap = std::max({A.bmin[k] - C.bmax[k], C.bmin[k] - A.bmax[k], 0.0});
+        d2 += gap * gap;
+      }
+      dist[f] = std::sqrt(d2);
+    }
+    for (int q = 0; q < nslot; ++q)
+      for (int f = 0; f < nfar; ++f)
+        zero_pair[size_t(q) * nfar + f] = underflows(dist[f], area, ctx->s[fr[q]] / ctx->c, H.dlp);
+  }
   std::vector<int> order(desc.size());
   std::iota(order.begin(), order.end(), 0);
   const bool predict = (flags & GCQ_FLAG_USE_PREDICTOR) != 0;
@@ -552,6 +592,7 @@ GCQ_API int gcq_aca_blocks(gcq_context* ctx, const int32_t* freq_idx, int32_t n_
     }
     order = order_desc_stable(cost);
   }
+  order.erase(std::remove_if(order.begin(), order.end(), [&](int p) { return zero_pair[p] != 0; }), order.end());
   std::vector<int> rank_aca, rank_out, status;
   std::vector<int64_t> off;
   int64_t pool_used = 0;
@@ -568,8 +609,9 @@ GCQ_API int gcq_aca_blocks(gcq_context* ctx, const int32_t* freq_idx, int32_t n_
     off.assign(desc.size(), 0);
     for (int q = 0; q < nslot; ++q) {
       std::vector<PairDesc> dq(desc.begin() + size_t(q) * nfar, desc.begin() + size_t(q + 1) * nfar);
-      std::vector<int> oq(nfar);
-      std::iota(oq.begin(), oq.end(), 0);
+      std::vector<int> oq;
+      for (int f = 0; f < nfar; ++f)
+        if (!zero_pair[size_t(q) * nfar + f]) oq.push_back(f);
       std::vector<int> ra, ro, stt;
       std::vector<int64_t> of;
       rc = precision == GCQ_C128

@@ -53,39 +53,96 @@ __device__ __forceinline__ cpx<T> cinv(cpx<T> a) {
 }
 
 // ---- wave64 reductions (every lane receives the result) --------------------
+// All lanes take part.  The steps are data-parallel moves on the vector unit
+// (row shifts within 16 lanes, then row broadcasts: lane 63 ends with the
+// result, which moves to every lane through scalar registers) instead of
+// cross-lane permutes through LDS: the ACA and recompression kernels are chains
+// of these reductions, and each permute waits for the LDS queue.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_or(int v, int other) {   // the moved value, `other` where there is none
+  return __builtin_amdgcn_update_dpp(other, v, CTRL, ROWS, 0xf, false);
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_or(double v, double other) {
+  const int64_t a = __builtin_bit_cast(int64_t, v), o = __builtin_bit_cast(int64_t, other);
+  const uint32_t lo = uint32_t(dpp_or<CTRL, ROWS>(int(uint32_t(a)), int(uint32_t(o))));
+  const uint32_t hi = uint32_t(dpp_or<CTRL, ROWS>(int(a >> 32), int(o >> 32)));
+  return __builtin_bit_cast(double, int64_t((uint64_t(hi) << 32) | lo));
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp_or(float v, float other) {
+  return __builtin_bit_cast(float, dpp_or<CTRL, ROWS>(__builtin_bit_cast(int, v), __builtin_bit_cast(int, other)));
+}
+constexpr int DPP_SHR1 = 0x111, DPP_SHR2 = 0x112, DPP_SHR4 = 0x114, DPP_SHR8 = 0x118;   // within rows of 16 lanes
+constexpr int DPP_BCAST15 = 0x142, DPP_BCAST31 = 0x143;   // a row's / half's last lane to the rows after it
+
+__device__ __forceinline__ int lane_of(int v, int l) { return __builtin_amdgcn_readlane(v, l); }
+__device__ __forceinline__ float lane_of(float v, int l) {
+  return __builtin_bit_cast(float, lane_of(__builtin_bit_cast(int, v), l));
+}
+__device__ __forceinline__ double lane_of(double v, int l) {
+  const int64_t a = __builtin_bit_cast(int64_t, v);
+  const uint32_t lo = uint32_t(lane_of(int(uint32_t(a)), l)), hi = uint32_t(lane_of(int(a >> 32), l));
+  return __builtin_bit_cast(double, int64_t((uint64_t(hi) << 32) | lo));
+}
+// op over the wave; `none` is op's neutral value
+template <typename V, typename Op>
+__device__ __forceinline__ V wave_reduce(V v, V none, Op op) {
+  v = op(v, dpp_or<DPP_SHR1, 0xf>(v, none));
+  v = op(v, dpp_or<DPP_SHR2, 0xf>(v, none));
+  v = op(v, dpp_or<DPP_SHR4, 0xf>(v, none));
+  v = op(v, dpp_or<DPP_SHR8, 0xf>(v, none));
+  v = op(v, dpp_or<DPP_BCAST15, 0xa>(v, none));
+  v = op(v, dpp_or<DPP_BCAST31, 0xc>(v, none));
+  return lane_of(v, WAVE - 1);
+}
 __device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, WAVE);
-  return v;
+  return wave_reduce(v, 0.0, [](double a, double b) { return a + b; });
 }
 __device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, WAVE);
-  return v;
+  return wave_reduce(v, 0.f, [](float a, float b) { return a + b; });
+}
+__device__ __forceinline__ double wave_max(double v) {
+  return wave_reduce(v, -1e300, [](double a, double b) { return fmax(a, b); });
 }
 __device__ __forceinline__ int wave_min_int(int v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = min(v, __shfl_xor(v, o, WAVE));
-  return v;
+  return wave_reduce(v, 0x7fffffff, [](int a, int b) { return min(a, b); });
 }
-__device__ __forceinline__ int wave_max_int(int v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o, WAVE));
-  return v;
+// four sums at once: the halves, then the rows of the wave are exchanged between
+// the four values, so that one row of 16 lanes is left of each
+__device__ __forceinline__ void wave_sum4(double& a, double& b, double& c, double& d) {
+  auto swap = [](double& x, double& y, auto f) {
+    const int64_t p = __builtin_bit_cast(int64_t, x), q = __builtin_bit_cast(int64_t, y);
+    const auto lo = f(uint32_t(p), uint32_t(q)), hi = f(uint32_t(p >> 32), uint32_t(q >> 32));
+    x = __builtin_bit_cast(double, int64_t((uint64_t(hi[0]) << 32) | lo[0]));
+    y = __builtin_bit_cast(double, int64_t((uint64_t(hi[1]) << 32) | lo[1]));
+  };
+  auto half = [](uint32_t x, uint32_t y) { return __builtin_amdgcn_permlane32_swap(x, y, false, false); };
+  auto row = [](uint32_t x, uint32_t y) { return __builtin_amdgcn_permlane16_swap(x, y, false, false); };
+  swap(a, c, half);
+  swap(b, d, half);
+  a += c;   // halves: sums of a | of c
+  b += d;   // of b | of d
+  swap(a, b, row);
+  a += b;   // rows: a, b, c, d
+  a += dpp_or<DPP_SHR1, 0xf>(a, 0.0);
+  a += dpp_or<DPP_SHR2, 0xf>(a, 0.0);
+  a += dpp_or<DPP_SHR4, 0xf>(a, 0.0);
+  a += dpp_or<DPP_SHR8, 0xf>(a, 0.0);
+  const double s = a;
+  a = lane_of(s, 15);
+  b = lane_of(s, 31);
+  c = lane_of(s, 47);
+  d = lane_of(s, 63);
 }
 // argmax of (val, idx) pairs: largest val, lowest idx among equal vals.
 // Lanes without a candidate pass val = -1.
-template <typename T>
-__device__ __forceinline__ void wave_argmax(T& val, int& idx) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    T ov = __shfl_xor(val, o, WAVE);
-    int oi = __shfl_xor(idx, o, WAVE);
-    if (ov > val || (ov == val && oi < idx)) {
-      val = ov;
-      idx = oi;
-    }
-  }
+__device__ __forceinline__ void wave_argmax(double& val, int& idx) {
+  const double m = wave_max(val);
+  const uint64_t at = __ballot(val == m);
+  idx = (at & (at - 1)) == 0 ? lane_of(idx, __ffsll((unsigned long long)at) - 1)
+                             : wave_min_int(val == m ? idx : 0x7fffffff);
+  val = m;
 }
 
 // ---- wave-uniform values ----------------------------------------------------

@@ -259,24 +259,41 @@ __device__ int aca_grp(Ent& ent, int m, int n, int cap, int max_rank, double tol
       }
     }
     __syncthreads();
-    // Gram entries of the new term: entry l by wave l mod NW
+    // Gram entries of the new term: entry l by wave l mod NW; the first GRAM_R
+    // rows of the new vectors stay in registers
+    constexpr int GRAM_R = 2;
+    cpx<T> bu[GRAM_R], bw[GRAM_R];
+    if (wid < k) {
+#pragma unroll
+      for (int q = 0; q < GRAM_R; ++q) {
+        const int r = lane + q * WAVE;
+        bu[q] = r < m ? U[int64_t(k) * m + r] : cpx<T>{T(0), T(0)};
+        bw[q] = r < n ? W[int64_t(k) * n + r] : cpx<T>{T(0), T(0)};
+      }
+    }
     double crossw = 0.0;
     for (int l = wid; l < k; l += NW) {
       double gur = 0, gui = 0, gwr = 0, gwi = 0;
-      for (int r = lane; r < m; r += WAVE) {
-        cpx<T> a = U[int64_t(l) * m + r], b = U[int64_t(k) * m + r];
-        gur += double(a.re) * b.re + double(a.im) * b.im;
-        gui += double(a.re) * b.im - double(a.im) * b.re;
+      auto dot = [](cpx<T> a, cpx<T> b, double& re, double& im) {   // += conj(a) b
+        re += double(a.re) * b.re + double(a.im) * b.im;
+        im += double(a.re) * b.im - double(a.im) * b.re;
+      };
+      cpx<T> au[GRAM_R], aw[GRAM_R];
+#pragma unroll
+      for (int q = 0; q < GRAM_R; ++q) {   // (clamped rows meet zeros)
+        au[q] = U[int64_t(l) * m + min(lane + q * WAVE, m - 1)];
+        aw[q] = W[int64_t(l) * n + min(lane + q * WAVE, n - 1)];
       }
-      for (int j = lane; j < n; j += WAVE) {
-        cpx<T> a = W[int64_t(l) * n + j], b = W[int64_t(k) * n + j];
-        gwr += double(a.re) * b.re + double(a.im) * b.im;
-        gwi += double(a.re) * b.im - double(a.im) * b.re;
+#pragma unroll
+      for (int q = 0; q < GRAM_R; ++q) {
+        dot(au[q], bu[q], gur, gui);
+        dot(aw[q], bw[q], gwr, gwi);
       }
-      gur = wave_sum(gur);
-      gui = wave_sum(gui);
-      gwr = wave_sum(gwr);
-      gwi = wave_sum(gwi);
+      for (int r = lane + GRAM_R * WAVE; r < m; r += WAVE)
+        dot(U[int64_t(l) * m + r], U[int64_t(k) * m + r], gur, gui);
+      for (int j = lane + GRAM_R * WAVE; j < n; j += WAVE)
+        dot(W[int64_t(l) * n + j], W[int64_t(k) * n + j], gwr, gwi);
+      wave_sum4(gur, gui, gwr, gwi);
       crossw += gur * gwr - gui * gwi;  // Re((u_l^H u_k)(w_l^H w_k))
       if (lane == 0) {
         GU[l * cap + k] = {gur, gui};

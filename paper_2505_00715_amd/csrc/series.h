@@ -97,12 +97,6 @@ __device__ __forceinline__ void cexp_to(double r, double2 s, double& re, double&
     cexp_pair(r, s, re, im);
 }
 
-__device__ __forceinline__ double wave_max(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, WAVE));
-  return v;
-}
-
 // exp(-sigma r0) times the polynomial's value (and derivative), as above
 template <typename T, bool DLP, int D, typename Coef>
 __device__ __forceinline__ void series_eval(const Coef& c, double r0, double h, double2 s, double& re, double& im) {
