@@ -4,6 +4,7 @@
 #include <cmath>
 #include <cstring>
 #include <numeric>
+#include <type_traits>
 
 #include "internal.h"
 #include "lowrank.h"
@@ -25,6 +26,22 @@ struct PlainEntry {
   }
 };
 
+// A work queue of n items in eight parts (items i, i + 8, ..), each with a counter in
+// a memory channel of its own: one counter for 1e5 short pairs was the bound of
+// the smallest classes (an atomic on one address takes about 10 ns, and every one
+// goes to memory).  A group starts at its own part and goes on to the others; one
+// thread calls; n when all are taken.
+constexpr int QUEUE_PARTS = 8, QUEUE_STRIDE = 64;   // (ints: 256 bytes)
+constexpr int QUEUE_INTS = QUEUE_PARTS * QUEUE_STRIDE;
+__device__ __forceinline__ int queue_next(int* __restrict__ counter, int n, int home, int& visited) {
+  for (; visited < QUEUE_PARTS; ++visited) {
+    const int q = (home + visited) % QUEUE_PARTS;
+    const int i = atomicAdd(counter + q * QUEUE_STRIDE, 1) * QUEUE_PARTS + q;
+    if (i < n) return i;
+  }
+  return n;
+}
+
 // ALLFAR = true serves the pairs of blocks without self/near-tier entries,
 // ALLFAR = false the others; each instance skips the pairs of the other kind.
 // NW waves work on one pair together; DLP: entries of the double layer.
@@ -38,14 +55,15 @@ __global__ void __launch_bounds__(NW * 64, NW == 1 && ALLFAR && sizeof(T) == 4 ?
   __shared__ AcaShared<T> sm;
   __shared__ int slot;
   const int tid = threadIdx.x;
+  int visited = 0;
   for (;;) {
     int idx;
     if constexpr (NW == 1) {
       idx = 0;
-      if (tid == 0) idx = atomicAdd(counter, 1);
-      idx = __shfl(idx, 0, WAVE);
+      if (tid == 0) idx = queue_next(counter, npairs, blockIdx.x, visited);
+      idx = uni(idx);
     } else {
-      if (tid == 0) slot = atomicAdd(counter, 1);
+      if (tid == 0) slot = queue_next(counter, npairs, blockIdx.x, visited);
       __syncthreads();
       idx = uni(slot);
       __syncthreads();
@@ -98,9 +116,8 @@ __device__ __forceinline__ int rank_class(int k) {
 }
 
 // the pairs of each class, in one list (class by class): cls[0 .. RC_N) the
-// class sizes, cls[RC_N .. 2 RC_N) scatter cursors, cls[2 RC_N .. 3 RC_N)
-// the classes' queue heads, all zero on entry; pass 0 counts, pass 1
-// scatters (the class offsets are the sums of the sizes before)
+// class sizes, cls[RC_N .. 2 RC_N) scatter cursors, zero on entry; pass 0
+// counts, pass 1 scatters (the class offsets are the sums of the sizes before)
 __global__ void __launch_bounds__(256) recompress_classify(const int* __restrict__ rank, int nc,
                                                            int* __restrict__ cls, int* __restrict__ list,
                                                            int pass) {
@@ -134,8 +151,9 @@ __global__ void __launch_bounds__(NW * 64) recompress_kernel(const PairDesc* __r
                                                              const int* __restrict__ rank_in,
                                                              int* __restrict__ out_t, double tol,
                                                              int do_recompress, unsigned char* __restrict__ jws,
-                                                             int c, int* __restrict__ cls,
-                                                             const int* __restrict__ list) {
+                                                             int c, const int* __restrict__ cls,
+                                                             const int* __restrict__ list,
+                                                             int* __restrict__ queue) {
   __shared__ cpx<double> mats[GL ? 1 : recompress_mats(MK)];
   __shared__ RecompSharedT<MK> rs;
   __shared__ int slot;
@@ -143,9 +161,10 @@ __global__ void __launch_bounds__(NW * 64) recompress_kernel(const PairDesc* __r
   int off = 0;
   for (int r = 0; r < c; ++r) off += cls[r];
   const int size = cls[c];
+  int visited = 0;
   for (;;) {
     __syncthreads();
-    if (threadIdx.x == 0) slot = atomicAdd(cls + 2 * RC_N + c, 1);
+    if (threadIdx.x == 0) slot = queue_next(queue, size, blockIdx.x, visited);
     __syncthreads();
     const int q = uni(slot);
     if (q >= size) break;
@@ -167,7 +186,7 @@ constexpr int RECOMP_GL_GRID = 1024;   // groups of the class whose matrices are
 template <typename T>
 static int launch_recompress(gcq_context* ctx, int nc, const PairDesc* pairs, unsigned char* ws,
                              const int* rank, int* t, double tol, int rec, unsigned char* jws, int* cls,
-                             int* list) {
+                             int* list, int* queues) {
   GCQ_TRY(ensure_side_streams(ctx));
   hipStream_t st = ctx->stream;
   const int cg = (nc + 255) / 256;
@@ -175,23 +194,24 @@ static int launch_recompress(gcq_context* ctx, int nc, const PairDesc* pairs, un
   hipLaunchKernelGGL(recompress_classify, dim3(cg), dim3(256), 0, st, rank, nc, cls, list, 1);
   GCQ_HIP(hipEventRecord(ctx->evfork, st));
   for (int i = 0; i < 3; ++i) GCQ_HIP(hipStreamWaitEvent(ctx->side[i], ctx->evfork, 0));
-  const int g1 = std::min(nc, 5120), g2 = std::min(nc, 2560), g4 = std::min(nc, 1024), g8 = std::min(nc, 512);
-  hipLaunchKernelGGL((recompress_kernel<T, 64, 4, true>), dim3(std::min(nc, RECOMP_GL_GRID)), dim3(256), 0,
-                     ctx->side[0], pairs, ws, rank, t, tol, rec, jws, 7, cls, list);
-  hipLaunchKernelGGL((recompress_kernel<T, 56, 8, false>), dim3(g8), dim3(512), 0, ctx->side[0], pairs, ws,
-                     rank, t, tol, rec, jws, 6, cls, list);
-  hipLaunchKernelGGL((recompress_kernel<T, 32, 4, false>), dim3(g4), dim3(256), 0, ctx->side[0], pairs, ws,
-                     rank, t, tol, rec, jws, 5, cls, list);
-  hipLaunchKernelGGL((recompress_kernel<T, 24, 2, false>), dim3(g2), dim3(128), 0, ctx->side[0], pairs, ws,
-                     rank, t, tol, rec, jws, 4, cls, list);
-  hipLaunchKernelGGL((recompress_kernel<T, 18, 2, false>), dim3(g2), dim3(128), 0, ctx->side[1], pairs, ws,
-                     rank, t, tol, rec, jws, 3, cls, list);
-  hipLaunchKernelGGL((recompress_kernel<T, 16, 2, false>), dim3(g2), dim3(128), 0, st, pairs, ws, rank, t, tol,
-                     rec, jws, 2, cls, list);
-  hipLaunchKernelGGL((recompress_kernel<T, 12, 1, false>), dim3(g1), dim3(64), 0, ctx->side[2], pairs, ws, rank,
-                     t, tol, rec, jws, 1, cls, list);
-  hipLaunchKernelGGL((recompress_kernel<T, 8, 1, false>), dim3(g1), dim3(64), 0, ctx->side[2], pairs, ws,
-                     rank, t, tol, rec, jws, 0, cls, list);
+  // The class to 56 goes first, on the context stream, which has no event to wait
+  // for: its workgroups need a compute unit's LDS to themselves, and behind the
+  // small classes, whose groups stay until their queues are empty, they would
+  // start when everything else is done.
+  auto go = [&](auto mk, auto nw, auto gl, int grid, hipStream_t s, int c) {
+    constexpr int MK = decltype(mk)::value, NW = decltype(nw)::value;
+    hipLaunchKernelGGL((recompress_kernel<T, MK, NW, decltype(gl)::value>), dim3(std::min(nc, grid)), dim3(64 * NW), 0,
+                       s, pairs, ws, rank, t, tol, rec, jws, c, (const int*)cls, (const int*)list, queues + c * QUEUE_INTS);
+  };
+  using std::integral_constant;
+  go(integral_constant<int, 56>(), integral_constant<int, 8>(), std::false_type(), 512, st, 6);
+  go(integral_constant<int, 32>(), integral_constant<int, 4>(), std::false_type(), 1024, ctx->side[0], 5);
+  go(integral_constant<int, 24>(), integral_constant<int, 2>(), std::false_type(), 2560, ctx->side[1], 4);
+  go(integral_constant<int, 12>(), integral_constant<int, 1>(), std::false_type(), 5120, ctx->side[2], 1);
+  go(integral_constant<int, 18>(), integral_constant<int, 2>(), std::false_type(), 2560, ctx->side[0], 3);
+  go(integral_constant<int, 16>(), integral_constant<int, 2>(), std::false_type(), 2560, ctx->side[1], 2);
+  go(integral_constant<int, 8>(), integral_constant<int, 1>(), std::false_type(), 5120, ctx->side[2], 0);
+  go(integral_constant<int, 64>(), integral_constant<int, 4>(), std::true_type(), RECOMP_GL_GRID, st, 7);
   GCQ_HIP(hipGetLastError());
   for (int i = 0; i < 3; ++i) {
     GCQ_HIP(hipEventRecord(ctx->evjoin[i], ctx->side[i]));
@@ -305,14 +325,18 @@ static int run_aca_pairs(gcq_context* ctx, std::vector<PairDesc>& desc, std::vec
     for (int a = 0; a < nc; ++a) cd[a] = desc[chunk[a]];
     GCQ_TRY(ctx->scratchA.ensure(size_t(wsz) + 256));
     GCQ_TRY(upload(ctx->scratchB, cd, st));
-    GCQ_TRY(ctx->scratchC.ensure(sizeof(int) * (4 * size_t(nc) + 32)));
-    int* d_rank = ctx->scratchC.as<int>();
+    // queues of the two ACA launches and of the rank classes, class sizes and
+    // cursors, then ranks, status, truncated ranks and the pairs class by class
+    constexpr int NCTR = (2 + RC_N) * QUEUE_INTS + 2 * RC_N;
+    GCQ_TRY(ctx->scratchC.ensure(sizeof(int) * (4 * size_t(nc) + NCTR)));
+    int* d_counter = ctx->scratchC.as<int>();
+    int* d_queues = d_counter + 2 * QUEUE_INTS;
+    int* d_cls = d_queues + RC_N * QUEUE_INTS;
+    int* d_rank = d_counter + NCTR;
     int* d_status = d_rank + nc;
     int* d_t = d_status + nc;
-    int* d_counter = d_t + nc;
-    int* d_cls = d_counter + 8;      // rank classes of the recompression (3 x 8 counters)
-    int* d_list = d_counter + 32;    // the pairs class by class
-    hipLaunchKernelGGL(zero_int, dim3(1), dim3(64), 0, st, d_counter, 32);
+    int* d_list = d_t + nc;
+    hipLaunchKernelGGL(zero_int, dim3((NCTR + 255) / 256), dim3(256), 0, st, d_counter, NCTR);
     int nnf = 0;
     for (int a = 0; a < nc; ++a) nnf += cd[a].all_far == 0;
     const int nw = ctx->tune.aca_waves;
@@ -327,14 +351,14 @@ static int run_aca_pairs(gcq_context* ctx, std::vector<PairDesc>& desc, std::vec
       launch_aca<T, false>(ctx->H.dlp, nw, std::min(grid, nnf), st, ctx->tab(),
                            (const PairDesc*)ctx->scratchB.as<PairDesc>(), (const int*)nullptr, nc,
                            ctx->scratchA.as<unsigned char>(), tol, max_rank, d_rank, d_status,
-                           d_counter + 1);
+                           d_counter + QUEUE_INTS);
     GCQ_HIP(hipGetLastError());
     // the recompression follows on the device without a host round trip; the
     // split event divides the region between the two
     GCQ_HIP(hipEventRecord(ctx->evm, st));
     // recompression by rank classes; matrices above 56 terms live in global scratch
     GCQ_TRY(launch_recompress<T>(ctx, nc, ctx->scratchB.as<PairDesc>(), ctx->scratchA.as<unsigned char>(), d_rank,
-                                 d_t, tol, recompress ? 1 : 0, ctx->scratchD.as<unsigned char>(), d_cls, d_list));
+                                 d_t, tol, recompress ? 1 : 0, ctx->scratchD.as<unsigned char>(), d_cls, d_list, d_queues));
     GCQ_HIP(hipGetLastError());
     {
       double a = 0.0, r = 0.0;

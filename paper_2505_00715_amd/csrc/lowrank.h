@@ -280,8 +280,8 @@ __device__ int aca_grp(Ent& ent, int m, int n, int cap, int max_rank, double tol
       };
       cpx<T> au[GRAM_R], aw[GRAM_R];
 #pragma unroll
-      for (int q = 0; q < GRAM_R; ++q) {   // (clamped rows meet zeros)
-        au[q] = U[int64_t(l) * m + min(lane + q * WAVE, m - 1)];
+      for (int q = 0; q < GRAM_R; ++q) {
+        au[q] = U[int64_t(l) * m + min(lane + q * WAVE, m - 1)];   // (clamped rows meet zeros)
         aw[q] = W[int64_t(l) * n + min(lane + q * WAVE, n - 1)];
       }
 #pragma unroll
@@ -340,6 +340,10 @@ __device__ inline int aca_wave(Ent& ent, int m, int n, int cap, int max_rank, do
   return aca_grp<1, false, T, Ent>(ent, m, n, cap, max_rank, tol, nu, U, W, GU, GV, sm, status);
 }
 
+// e / k for 0 <= e < 4096, 1 <= k <= 64, with mul = quot_mul(k)
+__device__ __forceinline__ unsigned quot_mul(int k) { return (unsigned(1 << 18) + k - 1) / k; }
+__device__ __forceinline__ int quot(int e, unsigned mul) { return int((unsigned(e) * mul) >> 18); }
+
 // ---- Hermitian Jacobi eigen-solver, one group, k <= 64 ------------------------
 // A (k x k, row-major, generic memory) is overwritten by its eigenvalues on the
 // diagonal; Q (k x k) receives the eigenvectors as columns.  Each rotation is
@@ -363,7 +367,8 @@ __device__ __attribute__((always_inline)) inline void jacobi_grp(cpx<double>* A,
                                                                  int k, RS& rs, double thr) {
   constexpr int NT = NW * WAVE;
   const int tid = threadIdx.x;
-  for (int r = tid; r < k * k; r += NT) Q[r] = {(r / k == r % k) ? 1.0 : 0.0, 0.0};
+  const unsigned mk = quot_mul(k);
+  for (int r = tid; r < k * k; r += NT) Q[r] = {quot(r, mk) * (k + 1) == r ? 1.0 : 0.0, 0.0};
   __syncthreads();
   if (k < 2) return;
   const int ke = (k + 1) & ~1;   // even number of positions (one dummy when k is odd)
@@ -375,7 +380,7 @@ __device__ __attribute__((always_inline)) inline void jacobi_grp(cpx<double>* A,
     double off = 0.0, dg = 0.0;
     for (int r = tid; r < k * k; r += NT) {
       double v = cabs2(A[r]);
-      if (r / k == r % k) dg += v;
+      if (quot(r, mk) * (k + 1) == r) dg += v;
       else off += v;
     }
     grp_sum2<NW>(off, dg);
@@ -499,7 +504,11 @@ __device__ __attribute__((always_inline)) inline void jacobi_grp(cpx<double>* A,
 //   3. Keep the smallest t with sqrt(sum_{i >= t} s_i^2) <= tol max(sqrt(sum s_i^2), nu):
 //      Ubar = U CU, CU = R^H Z_t;  Vbar = V CV, CV = R^+ Z_t, R^+ the right
 //      inverse of R supported on the pivot rows (triangular solve).
-// CU and CV (k x t, leading dimension t) are written over GU and GV.  Without
+// The Gram matrices are copied to the working memory before they are multiplied,
+// and the triangular solve runs there, a row of all t columns after the other:
+// read and written in place in global memory the two took 60% of the
+// recompression's time.  CU and CV (k x t, leading dimension t) are written over
+// GU and GV.  Without
 // recompression CU = CV = I, t = k.  Returns t.
 // Always inlined, for the reason given at jacobi_grp.
 template <int NW, typename RS>
@@ -518,11 +527,14 @@ __device__ __attribute__((always_inline)) inline int recompress_grp(
     return k;
   }
   cpx<double>* S = mats;           // k x k Schur complement of G_V, then R (rows in pivot order)
-  cpx<double>* B = S + k * k;      // r x r
+  cpx<double>* B = S + k * k;      // G_U (k x k), then r x r
   cpx<double>* Z = B + k * k;      // r x r
-  cpx<double>* R = Z;              // rows of R are built in Z first (B, Z are free until step 2)
+  cpx<double>* R = Z;              // rows of R are built in Z first (free until step 2)
+  const unsigned mk = quot_mul(k);
   for (int e = tid; e < k * k; e += NT) {
-    S[e] = GV[(e / k) * cap + (e % k)];
+    const int a = quot(e, mk), b2 = e - a * k;
+    S[e] = GV[a * cap + b2];
+    B[e] = GU[a * cap + b2];
     R[e] = {0.0, 0.0};
   }
   if (tid < k) rs.keep[tid] = 0;   // eliminated flags
@@ -571,7 +583,7 @@ __device__ __attribute__((always_inline)) inline int recompress_grp(
     __syncthreads();
     // S[a][b] -= conj(R[r][a]) R[r][b] over remaining a, b
     for (int e = tid; e < k * k; e += NT) {
-      const int a = e / k, b2 = e % k;
+      const int a = quot(e, mk), b2 = e - a * k;
       if (rs.keep[a] || rs.keep[b2]) continue;
       const cpx<double> x = R[r * k + a], y = R[r * k + b2];
       S[e].re -= x.re * y.re + x.im * y.im;
@@ -581,13 +593,14 @@ __device__ __attribute__((always_inline)) inline int recompress_grp(
   }
   if (r == 0) return 0;
   // keep R (r x k) in S, then B = R G_U R^H: T1 = G_U R^H (k x r) into Z first
+  const unsigned mr = quot_mul(r);
   for (int e = tid; e < r * k; e += NT) S[e] = R[e];
   __syncthreads();
   for (int e = tid; e < k * r; e += NT) {
-    const int x = e / r, b2 = e % r;
+    const int x = quot(e, mr), b2 = e - x * r;
     cpx<double> acc = {0, 0};
     for (int y = 0; y < k; ++y) {
-      const cpx<double> g = GU[x * cap + y], rr = S[b2 * k + y];
+      const cpx<double> g = B[x * k + y], rr = S[b2 * k + y];
       acc.re += g.re * rr.re + g.im * rr.im;   // g conj(rr)
       acc.im += g.im * rr.re - g.re * rr.im;
     }
@@ -595,7 +608,7 @@ __device__ __attribute__((always_inline)) inline int recompress_grp(
   }
   __syncthreads();
   for (int e = tid; e < r * r; e += NT) {
-    const int a = e / r, b2 = e % r;
+    const int a = quot(e, mr), b2 = e - a * r;
     cpx<double> acc = {0, 0};
     for (int x = 0; x < k; ++x) {
       const cpx<double> p = cmul(S[a * k + x], Z[x * r + b2]);
@@ -606,7 +619,7 @@ __device__ __attribute__((always_inline)) inline int recompress_grp(
   }
   __syncthreads();
   for (int e = tid; e < r * r; e += NT) {  // Hermitian part
-    const int a = e / r, b2 = e % r;
+    const int a = quot(e, mr), b2 = e - a * r;
     if (a < b2) {
       cpx<double> x = B[a * r + b2], y = B[b2 * r + a];
       cpx<double> h = {0.5 * (x.re + y.re), 0.5 * (x.im - y.im)};
@@ -646,9 +659,11 @@ __device__ __attribute__((always_inline)) inline int recompress_grp(
   }
   __syncthreads();
   const int t = uni(rs.tcut);
-  // CU = R^H Z_t (k x t) over GU
+  if (t == 0) return 0;
+  // CU = R^H Z_t (k x t) over GU, and Z_t (r x t) into B for the solve
+  const unsigned mt = quot_mul(t);
   for (int e = tid; e < k * t; e += NT) {
-    const int x = e / t, c = e % t;
+    const int x = quot(e, mt), c = e - x * t;
     const int zc = rs.keep[c];
     cpx<double> acc = {0, 0};
     for (int a = 0; a < r; ++a) {
@@ -657,22 +672,31 @@ __device__ __attribute__((always_inline)) inline int recompress_grp(
       acc.im += p.im;
     }
     GU[e] = acc;
+    if (x < r) B[e] = Z[x * r + zc];
+    GV[e] = {0.0, 0.0};
   }
-  // CV: rows order[j] of R_P^{-1} Z_t, R_P[i][j] = R[i][order[j]] upper triangular
-  for (int e = tid; e < k * t; e += NT) GV[e] = {0.0, 0.0};
+  // CV: rows order[j] of R_P^{-1} Z_t, R_P[i][j] = R[i][order[j]] upper triangular:
+  // row i of the solution, then its part in the rows above
   __syncthreads();
-  for (int c = tid; c < t; c += NT) {
-    const int zc = rs.keep[c];
-    for (int i = r - 1; i >= 0; --i) {
-      cpx<double> acc = Z[i * r + zc];
-      for (int j = i + 1; j < r; ++j) {
-        const cpx<double> p = cmul(S[i * k + rs.order[j]], GV[rs.order[j] * t + c]);
-        acc.re -= p.re;
-        acc.im -= p.im;
-      }
-      const double dii = S[i * k + rs.order[i]].re;   // real positive pivot
-      GV[rs.order[i] * t + c] = {acc.re / dii, acc.im / dii};
+  for (int i = r - 1; i >= 0; --i) {
+    const int oi = rs.order[i];
+    const double dii = S[i * k + oi].re;   // real positive pivot
+    for (int c = tid; c < t; c += NT) {
+      const cpx<double> v = B[i * t + c];
+      B[i * t + c] = {v.re / dii, v.im / dii};
     }
+    __syncthreads();
+    for (int e = tid; e < i * t; e += NT) {
+      const int j = quot(e, mt), c = e - j * t;
+      const cpx<double> p = cmul(S[j * k + oi], B[i * t + c]);
+      B[e].re -= p.re;
+      B[e].im -= p.im;
+    }
+    __syncthreads();
+  }
+  for (int e = tid; e < r * t; e += NT) {
+    const int i = quot(e, mt);
+    GV[rs.order[i] * t + (e - i * t)] = B[e];
   }
   __syncthreads();
   return t;
