@@ -57,7 +57,7 @@ struct RecompSharedT {
   int keep[MK], order[MK];
   int nkeep, tcut;
   // one round of the parallel Jacobi ordering, per index pair i: the rotation
-  // {c, s, Re e, Im e} (the identity when the pair is not rotated), the new
+  // {c, Re sigma, Im sigma, -} (the identity when the pair is not rotated), the new
   // diagonal of the pair's 2 x 2 block, and the pair's indices p | q << 8
   double4 rot[NP];
   double2 dia[NP];
@@ -344,11 +344,30 @@ __device__ inline int aca_wave(Ent& ent, int m, int n, int cap, int max_rank, do
 __device__ __forceinline__ unsigned quot_mul(int k) { return (unsigned(1 << 18) + k - 1) / k; }
 __device__ __forceinline__ int quot(int e, unsigned mul) { return int((unsigned(e) * mul) >> 18); }
 
+// 1 / sqrt(x) to double rounding, x > 0 and finite: the hardware's estimate and
+// two Newton steps
+__device__ __forceinline__ double rsqrt_newton(double x) {
+  double y = __builtin_amdgcn_rsq(x);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) y = fma(y * fma(-x * y, y, 1.0), 0.5, y);
+  return y;
+}
+
+// [u, v] -> [c u - sc v, s u + c v], sc = conj(s)
+__device__ __forceinline__ void rotate(double c, cpx<double> s, cpx<double> sc, cpx<double>& u,
+                                       cpx<double>& v) {
+  const cpx<double> a = u, b = v;
+  u = {fma(c, a.re, fma(-sc.re, b.re, sc.im * b.im)),
+       fma(c, a.im, fma(-sc.re, b.im, -sc.im * b.re))};
+  v = {fma(c, b.re, fma(s.re, a.re, -s.im * a.im)), fma(c, b.im, fma(s.re, a.im, s.im * a.re))};
+}
+
 // ---- Hermitian Jacobi eigen-solver, one group, k <= 64 ------------------------
 // A (k x k, row-major, generic memory) is overwritten by its eigenvalues on the
-// diagonal; Q (k x k) receives the eigenvectors as columns.  Each rotation is
-// G = diag(1, conj(e)) R(c, s), which zeroes A[p][q] = |b| e with the real
-// rotation of the symmetric 2 x 2 problem [[a, |b|], [|b|, d]].  Sweeps use the
+// diagonal; Q (k x k) receives the eigenvectors as columns.  Each rotation zeroes
+// b = A[p][q]: with x = (d - a) / 2 (a, d the pair's diagonal) and
+// r = sqrt(x^2 + |b|^2), c^2 = (1 + |x| / r) / 2 and sigma = sign(x) b / (2 r c),
+// columns [u, v] -> [c u - conj(sigma) v, sigma u + c v].  Sweeps use the
 // round-robin (tournament) ordering: every round rotates k/2 disjoint index
 // pairs at once, so a sweep is k - 1 parallel rounds instead of k (k - 1) / 2
 // sequential rotations.  Rotations of one round commute (disjoint pairs), so the
@@ -357,8 +376,15 @@ __device__ __forceinline__ int quot(int e, unsigned mul) { return int((unsigned(
 // rotated: its b is set to zero, a change below the rounding of a and d), then
 // G^H A G by 2 x 2 blocks (rows of pair i, columns of pair j) and Q G by rows,
 // each thread applying the rotations of its blocks without branches (the
-// identity for pairs not rotated).  Sweeps stop when the off-diagonal squared
-// Frobenius norm is at most `thr` times the diagonal's.
+// identity for pairs not rotated); groups of four waves and more give each
+// update one half of the threads.  A round is a chain of latencies with k/2
+// lanes busy in its first phase, so that phase has no division and no library
+// square root: two reciprocal square roots, by the hardware's start and Newton
+// steps to double rounding.  (With division and square roots, and both updates on
+// every thread: 3D-ACA far kernel on 3648 triangles at 256 frequencies 22.9 ms, now
+// 20.9; on 5120 triangles at 64, 57.5 and 50.6.)
+// Sweeps stop when the off-diagonal squared Frobenius norm is at most `thr`
+// times the diagonal's.
 // Always inlined: callers pass A and Q either in LDS or in global memory, and
 // the accesses compile to LDS instructions only where the pointer's origin is
 // visible.
@@ -366,6 +392,8 @@ template <int NW, typename RS>
 __device__ __attribute__((always_inline)) inline void jacobi_grp(cpx<double>* A, cpx<double>* Q,
                                                                  int k, RS& rs, double thr) {
   constexpr int NT = NW * WAVE;
+  constexpr bool HALVES = NW >= 4;             // the two updates on one half of the waves each
+  constexpr int NU = HALVES ? NT / 2 : NT;     // threads of an update
   const int tid = threadIdx.x;
   const unsigned mk = quot_mul(k);
   for (int r = tid; r < k * k; r += NT) Q[r] = {quot(r, mk) * (k + 1) == r ? 1.0 : 0.0, 0.0};
@@ -373,9 +401,11 @@ __device__ __attribute__((always_inline)) inline void jacobi_grp(cpx<double>* A,
   if (k < 2) return;
   const int ke = (k + 1) & ~1;   // even number of positions (one dummy when k is odd)
   const int np = ke / 2;
-  // work items of the update phases: (i, j) = (x / np, x % np) for x = tid,
-  // tid + NT, ...; decomposed once and advanced with a carry
-  const int row0 = tid / np, j0 = tid % np, drow = NT / np, dj = NT % np;
+  // work items of the update phases: (i, j) = (x / np, x % np) for x = tu,
+  // tu + NU, ...; decomposed once and advanced with a carry
+  const int tu = HALVES && tid >= NU ? tid - NU : tid;
+  const bool do_a = !HALVES || tid < NU, do_q = !HALVES || tid >= NU;
+  const int row0 = tu / np, j0 = tu % np, drow = NU / np, dj = NU % np;
   for (int sweep = 0; sweep < 40; ++sweep) {
     double off = 0.0, dg = 0.0;
     for (int r = tid; r < k * k; r += NT) {
@@ -396,31 +426,38 @@ __device__ __attribute__((always_inline)) inline void jacobi_grp(cpx<double>* A,
         };
         int p = idx(tid), q = idx(ke - 1 - tid);
         if (p > q) { int t = p; p = q; q = t; }
-        double c = 1.0, sv = 0.0, a = 0.0, d = 0.0, tb = 0.0;
-        cpx<double> e = {1.0, 0.0};
+        double c = 1.0, a = 0.0, d = 0.0, tb = 0.0;
+        cpx<double> sg = {0.0, 0.0};
         if (q < k) {
-          const cpx<double> b = A[p * k + q];
+          cpx<double> b = A[p * k + q];
           a = A[p * k + p].re;
           d = A[q * k + q].re;
           const double bb2 = cabs2(b);
           if (bb2 > 1e-300 && bb2 > 1e-34 * fabs(a * d)) {
-            const double ib = rsqrt(bb2);   // 1 / |b|
-            const double tau = 0.5 * (d - a) * ib;
-            const double t = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
-            c = rsqrt(1.0 + t * t);
-            sv = t * c;
-            e = {b.re * ib, b.im * ib};
-            tb = t * (bb2 * ib);
+            double x = 0.5 * (d - a);
+            // scaled where x^2 would leave the range
+            const bool big = fabs(x) > 1e150;
+            const double sc = big ? 0x1p-500 : 1.0;
+            x *= sc;
+            b = {b.re * sc, b.im * sc};
+            const double b2 = cabs2(b);
+            const double ir = rsqrt_newton(fma(x, x, b2));   // 1 / r
+            const double c2 = fma(0.5 * fabs(x), ir, 0.5);
+            const double ic = rsqrt_newton(c2);
+            c = c2 * ic;
+            const double h = copysign(0.5 * ir * ic, x);
+            sg = {b.re * h, b.im * h};
+            tb = h * ic * b2 * (big ? 0x1p+500 : 1.0);       // tan |b|
           }
         }
-        rs.rot[tid] = {c, sv, e.re, e.im};
+        rs.rot[tid] = {c, sg.re, sg.im, 0.0};
         rs.dia[tid] = {a - tb, d + tb};
         rs.pq[tid] = p | (q << 8);
       }
       __syncthreads();
-      {   // G^H A G: block (rows of pair i, columns of pair j)
+      if (do_a) {   // G^H A G: block (rows of pair i, columns of pair j)
         int i = row0, j = j0;
-        for (int x = tid; x < np * np; x += NT) {
+        for (int x = tu; x < np * np; x += NU) {
           const int ci = i, cj = j;
           i += drow;
           j += dj;
@@ -442,27 +479,16 @@ __device__ __attribute__((always_inline)) inline void jacobi_grp(cpx<double>* A,
           cpx<double> apq = qjv ? A[pi * k + qj] : cpx<double>{0.0, 0.0};
           cpx<double> aqp = qiv ? A[qi * k + pj] : cpx<double>{0.0, 0.0};
           cpx<double> aqq = qiv && qjv ? A[qi * k + qj] : cpx<double>{0.0, 0.0};
-          {   // columns: [u, v] -> [c u - s conj(e) v, s u + c conj(e) v]
-            const double4 R = rs.rot[cj];
-            const cpx<double> ec = {R.z, -R.w};
-            cpx<double> ev = cmul(ec, apq);
-            const cpx<double> n0 = {R.x * app.re - R.y * ev.re, R.x * app.im - R.y * ev.im};
-            const cpx<double> n1 = {R.y * app.re + R.x * ev.re, R.y * app.im + R.x * ev.im};
-            ev = cmul(ec, aqq);
-            const cpx<double> n2 = {R.x * aqp.re - R.y * ev.re, R.x * aqp.im - R.y * ev.im};
-            const cpx<double> n3 = {R.y * aqp.re + R.x * ev.re, R.y * aqp.im + R.x * ev.im};
-            app = n0; apq = n1; aqp = n2; aqq = n3;
+          const double4 Rj = rs.rot[cj], Ri = rs.rot[ci];
+          {
+            const cpx<double> s = {Rj.y, Rj.z}, sc = {Rj.y, -Rj.z};
+            rotate(Rj.x, s, sc, app, apq);
+            rotate(Rj.x, s, sc, aqp, aqq);
           }
-          {   // rows: [u; v] -> [c u - s e v; s u + c e v]
-            const double4 R = rs.rot[ci];
-            const cpx<double> e = {R.z, R.w};
-            cpx<double> ev = cmul(e, aqp);
-            const cpx<double> n0 = {R.x * app.re - R.y * ev.re, R.x * app.im - R.y * ev.im};
-            const cpx<double> n2 = {R.y * app.re + R.x * ev.re, R.y * app.im + R.x * ev.im};
-            ev = cmul(e, aqq);
-            const cpx<double> n1 = {R.x * apq.re - R.y * ev.re, R.x * apq.im - R.y * ev.im};
-            const cpx<double> n3 = {R.y * apq.re + R.x * ev.re, R.y * apq.im + R.x * ev.im};
-            app = n0; apq = n1; aqp = n2; aqq = n3;
+          {   // rows: the conjugate
+            const cpx<double> s = {Ri.y, -Ri.z}, sc = {Ri.y, Ri.z};
+            rotate(Ri.x, s, sc, app, aqp);
+            rotate(Ri.x, s, sc, apq, aqq);
           }
           A[pi * k + pj] = app;
           if (qjv) A[pi * k + qj] = apq;
@@ -470,9 +496,9 @@ __device__ __attribute__((always_inline)) inline void jacobi_grp(cpx<double>* A,
           if (qiv && qjv) A[qi * k + qj] = aqq;
         }
       }
-      {   // Q G: row r, columns of pair j
+      if (do_q) {   // Q G: row r, columns of pair j
         int r = row0, j = j0;
-        for (int x = tid; x < k * np; x += NT) {
+        for (int x = tu; x < k * np; x += NU) {
           const int cr = r, cj = j;
           r += drow;
           j += dj;
@@ -481,11 +507,10 @@ __device__ __attribute__((always_inline)) inline void jacobi_grp(cpx<double>* A,
           const int p = pqj & 255, q = pqj >> 8;
           if (q >= k) continue;
           const double4 R = rs.rot[cj];
-          const cpx<double> ec = {R.z, -R.w};
-          const cpx<double> u = Q[cr * k + p], v = Q[cr * k + q];
-          const cpx<double> ev = cmul(ec, v);
-          Q[cr * k + p] = {R.x * u.re - R.y * ev.re, R.x * u.im - R.y * ev.im};
-          Q[cr * k + q] = {R.y * u.re + R.x * ev.re, R.y * u.im + R.x * ev.im};
+          cpx<double> u = Q[cr * k + p], v = Q[cr * k + q];
+          rotate(R.x, {R.y, R.z}, {R.y, -R.z}, u, v);
+          Q[cr * k + p] = u;
+          Q[cr * k + q] = v;
         }
       }
       __syncthreads();
