@@ -179,7 +179,7 @@ struct Faces3D {
   // products (built on first use, per block table d_bfblk)
   DevBuf bfpool, bftbuf, d_bfblk, d_bfitems, d_bfrange, d_bfrowblk, d_bfbig, d_bfmask;
   bool bf_valid = false;
-  int bf_items = 0, bf_big = 0, bf_levels = 0;
+  int bf_items = 0, bf_big = 0, bf_levels = 0, bf_nk = 4;
   int64_t bf_bytes = 0;
   ProductGraphs graphs;
   // the operator or the frequency set changed: captured products, the

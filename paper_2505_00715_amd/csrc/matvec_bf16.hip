@@ -134,31 +134,12 @@ __device__ __forceinline__ f16v rprod(uint4 ah, uint4 al, uint4 xh, uint4 xm, ui
   return c;
 }
 
-// one contraction step of 16 complex values (two groups per lane pair):
-// rr += Re a Re x, ii += Im a Im x, ri += Re a Im x + Im a Re x
-__device__ __forceinline__ void cstep(const BfGroup& a, const BfGroup3& x, f16v& rr, f16v& ii, f16v& ri) {
-  rr = rprod(a.hr, a.lr, x.hr, x.mr, x.lr, rr);
-  ii = rprod(a.hi, a.li, x.hi, x.mi, x.li, ii);
-  ri = rprod(a.hr, a.lr, x.hi, x.mi, x.li, ri);
-  ri = rprod(a.hi, a.li, x.hr, x.mr, x.lr, ri);
-}
-
-__device__ __forceinline__ BfGroup zero_group() {
-  BfGroup g;
-  g.hr = g.lr = g.hi = g.li = make_uint4(0, 0, 0, 0);
-  return g;
-}
-__device__ __forceinline__ BfGroup3 zero_group3() {
-  BfGroup3 g;
-  g.hr = g.mr = g.lr = g.hi = g.mi = g.li = make_uint4(0, 0, 0, 0);
-  return g;
-}
-
 __device__ __forceinline__ uint4 neg_bf(uint4 u) {
   return make_uint4(u.x ^ 0x80008000u, u.y ^ 0x80008000u, u.z ^ 0x80008000u, u.w ^ 0x80008000u);
 }
 
-// complex multiply-add straight into (re, im) accumulators:
+// one contraction step of 16 complex values (two groups per lane pair), straight
+// into (re, im) accumulators:
 // re += Re a Re x - Im a Im x (with a's Im planes negated), im += Re a Im x + Im a Re x
 __device__ __forceinline__ void cstep2(const BfGroup& a, const BfGroup3& x, f16v& re, f16v& im) {
   re = rprod(a.hr, a.lr, x.hr, x.mr, x.lr, re);
@@ -373,43 +354,56 @@ struct Tiles {
 template <int KW>
 __device__ __forceinline__ void t_tile(const uint4* __restrict__ Vg, const BfBlock& B, int t, const Tiles<KW>& C,
                                        int lane, int lr, int lh, f16v* re, f16v* im) {
-#pragma unroll
-  for (int u = 0; u < KW; ++u) re[u] = im[u] = f16_zero();
   const uint4* vf = Vg + int64_t(t) * B.KS * FRAG;
+  BfGroup na = load_op(vf, lane);
+  BfGroup3 nx[KW];
+#pragma unroll
+  for (int u = 0; u < KW; ++u) {
+    nx[u] = load_x(C.xk[u], B.g0 + min(lh, B.G - 1), lr);
+    re[u] = im[u] = f16_zero();
+  }
   for (int j = 0; j < B.KS; ++j) {
-    const int g = 2 * j + lh;
-    const BfGroup a = load_op(vf + int64_t(j) * FRAG, lane);
+    const int jn = min(j + 1, B.KS - 1), g = min(2 * jn + lh, B.G - 1);
+    const BfGroup a = na;
+    BfGroup3 x[KW];
+#pragma unroll
+    for (int u = 0; u < KW; ++u) x[u] = nx[u];
+    na = load_op(vf + int64_t(jn) * FRAG, lane);
 #pragma unroll
     for (int u = 0; u < KW; ++u) {
-      const BfGroup3 x = (g < B.G && C.kv[u]) ? load_x(C.xk[u], B.g0 + g, lr) : zero_group3();
-      cstep2(a, x, re[u], im[u]);
+      nx[u] = load_x(C.xk[u], B.g0 + g, lr);
+      cstep2(a, x[u], re[u], im[u]);
     }
   }
 }
 
-// fiber of stacked column c of block b at frequency position kp
-__device__ __forceinline__ cpx<float> fiber(const int64_t* __restrict__ cols, const cpx<float>* __restrict__ pool,
-                                            int col0, int c, int kp) {
-  return pool[cols[3 * (col0 + c) + 2] + kp];
+// row (stacked column of its tile) of an accumulator's element r, lane half lh
+__device__ __forceinline__ int acc_row(int r, int lh) { return 8 * (r >> 2) + 4 * lh + (r & 3); }
+
+// the lane's 16 fiber values of tile t (rows 32 t + acc_row, the lane's column at
+// frequency position kp); rows beyond the block's columns stand for the last one,
+// where T is zero.  Issued before the contraction that makes T, so that the two
+// dependent reads (offset, value) pass while it runs.
+__device__ __forceinline__ void fibers(const BfBlock& B, int t, int col0, const int64_t* __restrict__ cols,
+                                       const cpx<float>* __restrict__ pool, int kp, int lh, cpx<float>* f) {
+#pragma unroll
+  for (int r = 0; r < 16; ++r)
+    f[r] = pool[cols[3 * (col0 + min(32 * t + acc_row(r, lh), B.R - 1)) + 2] + kp];
 }
 
-// T' = F o T of the lane's 16 elements (rows 32 t + 8 (r / 4) + 4 h + r % 4, the lane's
-// column), as two vector groups (contraction steps s = 0, 1)
-__device__ __forceinline__ void t_prime(const f16v& re, const f16v& im, const BfBlock& B, int t, int col0,
-                                        const int64_t* __restrict__ cols, const cpx<float>* __restrict__ pool,
-                                        bool kin, int kp, int lh, BfGroup3& t0, BfGroup3& t1) {
+// T' = F o T of the lane's 16 elements, as two vector groups (contraction steps
+// s = 0, 1); zero beyond the block's columns and for columns that do not exist
+__device__ __forceinline__ void t_prime(const f16v& re, const f16v& im, const cpx<float>* f, const BfBlock& B,
+                                        int t, bool kin, int lh, BfGroup3& t0, BfGroup3& t1) {
 #pragma unroll
   for (int s = 0; s < 2; ++s) {
     cpx<float> v[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       const int r = 8 * s + e;
-      const int c = 32 * t + 8 * (r >> 2) + 4 * lh + (r & 3);
-      v[e] = {0.f, 0.f};
-      if (c < B.R && kin) {
-        const cpx<float> f = fiber(cols, pool, col0, c, kp);
-        v[e] = {f.re * re[r] - f.im * im[r], f.re * im[r] + f.im * re[r]};
-      }
+      const bool in = kin && 32 * t + acc_row(r, lh) < B.R;
+      v[e].re = in ? f[r].re * re[r] - f[r].im * im[r] : 0.f;
+      v[e].im = in ? f[r].re * im[r] + f[r].im * re[r] : 0.f;
     }
     (s == 0 ? t0 : t1) = make_group3(v);
   }
@@ -449,6 +443,68 @@ __device__ __forceinline__ void store_t(uint4* __restrict__ f, const BfGroup3& a
   f[320] = a.li;
 }
 
+// TG tiles of 32 stacked columns (from tile t0) of a block's T' into the T' buffer.
+// The fibers are read first, the right-hand side of the next contraction step
+// before the current one is multiplied, each Vbar fragment's successor right after
+// it; beyond the block's column groups the operator is zero, so that the last
+// group stands in.  Latency of the start and the end of each group of tiles: the
+// matrix cores are 34% busy (41k-triangle housing, 256 frequencies: 10.8 ms with four
+// waves a SIMD and no load ahead, 9.8 now; groups of three tiles instead of two:
+// 2% less before the fibers took the registers).
+template <int TG, int KW>
+__device__ __forceinline__ void tf_tiles(const uint4* __restrict__ Vg, const BfBlock& B, int t0, const Tiles<KW>& C,
+                                         int kt0, int nkt, int col0, const int64_t* __restrict__ cols,
+                                         const cpx<float>* __restrict__ pool, uint4* __restrict__ Tbuf, int lane,
+                                         int lr, int lh) {
+  f16v re[TG][KW], im[TG][KW];
+  cpx<float> fv[TG][KW][16];
+  BfGroup a[TG];
+  BfGroup3 nxt[KW];
+  const uint4* vf = Vg + int64_t(t0) * B.KS * FRAG;
+  auto xload = [&](int j) {
+    const int g = min(2 * j + lh, B.G - 1);
+#pragma unroll
+    for (int u = 0; u < KW; ++u) nxt[u] = load_x(C.xk[u], B.g0 + g, lr);
+  };
+  xload(0);
+#pragma unroll
+  for (int v = 0; v < TG; ++v) {
+    a[v] = load_op(vf + int64_t(v) * B.KS * FRAG, lane);
+#pragma unroll
+    for (int u = 0; u < KW; ++u) re[v][u] = im[v][u] = f16_zero();
+  }
+#pragma unroll
+  for (int v = 0; v < TG; ++v)
+#pragma unroll
+    for (int u = 0; u < KW; ++u) fibers(B, t0 + v, col0, cols, pool, C.kp[u], lh, fv[v][u]);
+  for (int j = 0; j < B.KS; ++j) {
+    const int jn = min(j + 1, B.KS - 1);
+    BfGroup3 x[KW];
+#pragma unroll
+    for (int u = 0; u < KW; ++u) x[u] = nxt[u];
+    xload(jn);
+#pragma unroll
+    for (int v = 0; v < TG; ++v) {
+#pragma unroll
+      for (int u = 0; u < KW; ++u) cstep2(a[v], x[u], re[v][u], im[v][u]);
+      a[v] = load_op(vf + (int64_t(v) * B.KS + jn) * FRAG, lane);
+    }
+  }
+#pragma unroll
+  for (int v = 0; v < TG; ++v) {
+    const int t = t0 + v;
+#pragma unroll
+    for (int u = 0; u < KW; ++u) {
+      if (!C.kv[u]) continue;
+      BfGroup3 p, q;
+      t_prime(re[v][u], im[v][u], fv[v][u], B, t, C.kin[u], lh, p, q);
+      uint4* f = Tbuf + (B.toff + int64_t(t * nkt + kt0 + u) * 2) * VFRAG + lane;
+      store_t(f, p);
+      store_t(f + VFRAG, q);
+    }
+  }
+}
+
 // T' of far blocks whose row cluster has more than BF_MC rows, into the T'
 // buffer ([t][kt][s][plane][lane]); one workgroup per block, blocks from the
 // workgroup's XCD list (ordered by column cluster, so that blocks in flight on
@@ -458,7 +514,7 @@ __device__ __forceinline__ void store_t(uint4* __restrict__ f, const BfGroup3& a
 // KW tiles
 constexpr int BF_TG = 2;
 template <int KW>
-__global__ void __launch_bounds__(KW == 1 ? 512 : 256, KW == 1 ? 4 : 1) bf_tfill(
+__global__ void __launch_bounds__(KW == 1 ? 512 : 256, KW == 1 ? 2 : 1) bf_tfill(
     const int* __restrict__ big, const int* __restrict__ range, int* __restrict__ counter,
     const BfBlock* __restrict__ bb, const uint4* __restrict__ bfp,
     const int* __restrict__ bcol, const int64_t* __restrict__ cols, const cpx<float>* __restrict__ pool,
@@ -476,41 +532,10 @@ __global__ void __launch_bounds__(KW == 1 ? 512 : 256, KW == 1 ? 4 : 1) bf_tfill
     for (int kt0 = w * KW; kt0 < nkt; kt0 += nw * KW) {
       if (!tiles_active<KW>(tmask, kt0, nkt)) continue;
       const Tiles<KW> C(kt0, nkt, L, lr, ng, colpos, Xg);
-      for (int t0 = 0; t0 < B.T; t0 += BF_TG) {
-        const int nt = min(BF_TG, B.T - t0);
-        f16v re[BF_TG][KW], im[BF_TG][KW];
-#pragma unroll
-        for (int v = 0; v < BF_TG; ++v)
-#pragma unroll
-          for (int u = 0; u < KW; ++u) re[v][u] = im[v][u] = f16_zero();
-        for (int j = 0; j < B.KS; ++j) {
-          const int g = 2 * j + lh;
-          BfGroup3 x[KW];
-#pragma unroll
-          for (int u = 0; u < KW; ++u) x[u] = (g < B.G && C.kv[u]) ? load_x(C.xk[u], B.g0 + g, lr) : zero_group3();
-#pragma unroll
-          for (int v = 0; v < BF_TG; ++v) {
-            if (v >= nt) break;
-            const BfGroup a = load_op(Vg + (int64_t(t0 + v) * B.KS + j) * FRAG, lane);
-#pragma unroll
-            for (int u = 0; u < KW; ++u) cstep2(a, x[u], re[v][u], im[v][u]);
-          }
-        }
-#pragma unroll
-        for (int v = 0; v < BF_TG; ++v) {
-          if (v >= nt) break;
-          const int t = t0 + v;
-#pragma unroll
-          for (int u = 0; u < KW; ++u) {
-            if (!C.kv[u]) continue;
-            BfGroup3 a, c;
-            t_prime(re[v][u], im[v][u], B, t, bcol[b], cols, pool, C.kin[u], C.kp[u], lh, a, c);
-            uint4* f = Tbuf + (B.toff + int64_t(t * nkt + kt0 + u) * 2) * VFRAG + lane;
-            store_t(f, a);
-            store_t(f + VFRAG, c);
-          }
-        }
-      }
+      int t0 = 0;
+      for (; t0 + BF_TG <= B.T; t0 += BF_TG)
+        tf_tiles<BF_TG, KW>(Vg, B, t0, C, kt0, nkt, bcol[b], cols, pool, Tbuf, lane, lr, lh);
+      for (; t0 < B.T; ++t0) tf_tiles<1, KW>(Vg, B, t0, C, kt0, nkt, bcol[b], cols, pool, Tbuf, lane, lr, lh);
     }
   }
 }
@@ -548,7 +573,10 @@ __device__ __forceinline__ void store_rows(const f16v* yre, const f16v* yim, int
 // registers; per 32 stacked columns of a block, T' (BIG: read from the T'
 // buffer, items of up to 32 BF_RTB rows; else computed here, items of up to
 // BF_MC rows), then Y += Ubar[rows, tile] T'; plain stores into the row
-// cluster's level buffer
+// cluster's level buffer.  Every load is issued ahead of its use (41k-triangle
+// housing, 256 frequencies, before and now: BIG 10.4 and 7.9 ms, 68% of the matrix
+// cores' time at 1.8 GHz; else 7.1 and 6.1 ms, bound by the chain contraction, fiber,
+// split, second contraction of a tile at two waves a SIMD)
 template <bool BIG, int KW>
 __global__ void __launch_bounds__(KW == 1 ? 512 : 256) bf_rows(
     const BfItem* __restrict__ items, const int* __restrict__ range, const int* __restrict__ rowblk,
@@ -574,50 +602,66 @@ __global__ void __launch_bounds__(KW == 1 ? 512 : 256) bf_rows(
       for (int u = 0; u < KW; ++u)
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) yre[u][rt] = yim[u][rt] = f16_zero();
+      if constexpr (BIG) {
+        // the halves h = (t, s) of the item's blocks in one sequence: T' of the next
+        // half is loaded before the current one is applied, each row tile's Ubar
+        // fragment of the next half right after the current one's use, across the
+        // blocks' ends too (row tiles beyond the item's stand for the last: loaded, not
+        // multiplied)
+        auto ufrag = [&](const BfBlock& X, int rt) {
+          return bfp + (X.off + int64_t(X.T) * X.KS + int64_t(rt0 + min(rt, nrt - 1)) * 2 * X.T) * FRAG;
+        };
+        BfBlock B = bb[rowblk[I.b0]];
+        BfGroup3 nxt[KW];
+        BfGroup a[RT];
+        auto tload = [&](const BfBlock& X, int h) {
+#pragma unroll
+          for (int u = 0; u < KW; ++u)
+            nxt[u] = load_t(Tbuf + (X.toff + int64_t((h >> 1) * nkt + kt0 + (C.kv[u] ? u : 0)) * 2 + (h & 1)) * VFRAG,
+                            lane);
+        };
+        tload(B, 0);
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) a[rt] = load_op(ufrag(B, rt), lane);
+        for (int bi = 0; bi < I.nb; ++bi) {
+          const BfBlock N = bb[rowblk[I.b0 + min(bi + 1, I.nb - 1)]];
+          for (int h = 0; h < 2 * B.T; ++h) {
+            BfGroup3 tv[KW];
+#pragma unroll
+            for (int u = 0; u < KW; ++u) tv[u] = nxt[u];
+            const bool in = h + 1 < 2 * B.T;
+            const BfBlock& X = in ? B : N;
+            const int hn = in ? h + 1 : 0;
+            tload(X, hn);
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) {
+              if (rt < nrt) {
+#pragma unroll
+                for (int u = 0; u < KW; ++u) cstep2(a[rt], tv[u], yre[u][rt], yim[u][rt]);
+              }
+              a[rt] = load_op(ufrag(X, rt) + hn * FRAG, lane);
+              asm volatile("" ::: "memory");
+            }
+          }
+          B = N;
+        }
+      } else
       for (int bi = 0; bi < I.nb; ++bi) {
         const int b = rowblk[I.b0 + bi];
         const BfBlock B = bb[b];
         const uint4* op = bfp + B.off * FRAG;
         const uint4* Ug = op + int64_t(B.T) * B.KS * FRAG;
-        if constexpr (BIG) {
-          // the block's T' halves (t, sd) in order, the next one loaded while
-          // the current one is applied; one row tile's fragments in flight (the
-          // compiler barriers keep the loads of all row tiles from being
-          // hoisted together, which would not fit the registers)
-          auto tload = [&](int h, BfGroup3* tv) {
-#pragma unroll
-            for (int u = 0; u < KW; ++u)
-              tv[u] = C.kv[u] ? load_t(Tbuf + (B.toff + int64_t((h >> 1) * nkt + kt0 + u) * 2 + (h & 1)) * VFRAG,
-                                       lane)
-                              : zero_group3();
-          };
-          BfGroup3 nxt[KW];
-          tload(0, nxt);
-          for (int h = 0; h < 2 * B.T; ++h) {
-            BfGroup3 tv[KW];
-#pragma unroll
-            for (int u = 0; u < KW; ++u) tv[u] = nxt[u];
-            if (h + 1 < 2 * B.T) tload(h + 1, nxt);
-            const int t = h >> 1, sd = h & 1;
-#pragma unroll
-            for (int rt = 0; rt < RT; ++rt) {
-              if (rt >= nrt) break;
-              const BfGroup a = load_op(Ug + ((int64_t(rt0 + rt) * B.T + t) * 2 + sd) * FRAG, lane);
-#pragma unroll
-              for (int u = 0; u < KW; ++u) cstep2(a, tv[u], yre[u][rt], yim[u][rt]);
-              asm volatile("" ::: "memory");
-            }
-          }
-          continue;
-        }
         for (int t = 0; t < B.T; ++t) {
           {
             f16v re[KW], im[KW];
+            cpx<float> fv[KW][16];
+#pragma unroll
+            for (int u = 0; u < KW; ++u) fibers(B, t, bcol[b], cols, pool, C.kp[u], lh, fv[u]);
             t_tile<KW>(op, B, t, C, lane, lr, lh, re, im);
             BfGroup3 t0[KW], t1[KW];
 #pragma unroll
             for (int u = 0; u < KW; ++u)
-              t_prime(re[u], im[u], B, t, bcol[b], cols, pool, C.kin[u], C.kp[u], lh, t0[u], t1[u]);
+              t_prime(re[u], im[u], fv[u], B, t, C.kin[u], lh, t0[u], t1[u]);
 #pragma unroll
             for (int rt = 0; rt < RT; ++rt) {
               if (rt >= nrt) break;
@@ -643,21 +687,25 @@ __global__ void __launch_bounds__(KW == 1 ? 512 : 256) bf_rows(
 // or all of its inadmissible blocks); each wave owns one 32-column frequency
 // tile, so that the waves of a workgroup take the same operator fragments at
 // about the same time.  Y += f_d o (D_d X_J) per term.  A wave reads X_J once per
-// block, not once per term: BF_NK contraction steps of it (8 column groups, a
+// block, not once per term: NK contraction steps of it (8 column groups, a
 // leaf's width) stay in registers over the block's terms, wider blocks pass in
-// several such pieces.  The operator's next fragment is loaded while the current
-// one is multiplied.  Two waves a SIMD: with four, X_J re-read per term, the
-// kernel was bound by those reads (71 GB per product of the 41k-triangle
-// housing at 256 frequencies; 18.4 -> 11.9 ms there, 4.3 -> 0.85 ms on 3648
-// triangles with the cut block lists below).  Plain stores into a near-field
-// level.
-constexpr int BF_NK = 4;
+// several such pieces.  Each operator fragment's successor in its register slot is
+// loaded right after its use: two or three steps ahead, over the ends of terms
+// and blocks; X_J of the next block during the last term.  Two waves a SIMD.
+// Bound by the matrix cores: 69% busy at the 1.8 GHz the chip keeps under this
+// load (41k-triangle housing, 256 frequencies: 18.4 ms with four waves a SIMD and
+// X_J read per term, 11.9 with X_J kept and one fragment ahead, now 11.1; 3648
+// triangles: 4.3, 0.85 and 0.67 ms).  Of the 32 x 16 tiles 45% is padding there
+// (clusters of 41 rows and columns).  Plain stores into a near-field level.
+template <int NK>
 __global__ void __launch_bounds__(BF_WAVES * 64, 2) bf_near(
     const BfItem* __restrict__ items, const int* __restrict__ range, const int* __restrict__ rowblk,
     const int* __restrict__ bterm, const int64_t* __restrict__ tfoff, const cpx<float>* __restrict__ pool,
     const BfBlock* __restrict__ bb, const uint4* __restrict__ bfp, const int* __restrict__ colpos, int L, int ng,
     const uint4* __restrict__ Xg, cpx<float>* __restrict__ Ylev, int64_t lev_stride, int* __restrict__ counter,
     const int* __restrict__ tmask) {
+  constexpr int NS = NK == 4 ? 2 : 3;   // operator fragments in flight (of 16 registers)
+  static_assert(NK % NS == 0, "a step's slot is the same in every term");
   __shared__ int cur;
   const int lane = threadIdx.x & 63, lr = lane & 31, lh = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
@@ -670,41 +718,73 @@ __global__ void __launch_bounds__(BF_WAVES * 64, 2) bf_near(
       if (tmask && !tmask[kt]) continue;
       const Tiles<1> C(kt, nkt, L, lr, ng, colpos, Xg);
       f16v yre = f16_zero(), yim = f16_zero();
-      for (int bi = 0; bi < I.nb; ++bi) {
-        const int b = rowblk[I.b0 + bi];
-        const BfBlock B = bb[b];
+      BfGroup a[NS];
+      BfGroup3 x[NK];
+      // a piece: contraction steps j0 .. j0 + ks of a block; its first fragment
+      int bi = 0, j0 = 0, b = rowblk[I.b0];
+      BfBlock B = bb[b];
+      const uint4* df = bfp + (B.off + int64_t(rt) * B.KS) * FRAG;
+      auto xload = [&](const BfBlock& X, int j) {
+        return load_x(C.xk[0], X.g0 + min(2 * j + lh, X.G - 1), lr);
+      };
+#pragma unroll
+      for (int j = 0; j < NK; ++j) {
+        if (j < NS) a[j] = load_op(df + min(j, B.KS - 1) * FRAG, lane);
+        x[j] = xload(B, min(j, B.KS - 1));
+      }
+      for (bool more = true; more;) {
+        const int ks = min(NK, B.KS - j0);
         const int d0 = bterm[b], nd = bterm[b + 1] - d0;
         const int64_t dstep = int64_t(B.mt) * B.KS * FRAG;   // between two terms' fragments
-        for (int j0 = 0; j0 < B.KS; j0 += BF_NK) {
-          const int ks = min(BF_NK, B.KS - j0);
-          const uint4* df = bfp + B.off * FRAG + (int64_t(rt) * B.KS + j0) * FRAG;
-          BfGroup nxt = load_op(df, lane);
-          BfGroup3 x[BF_NK];
-#pragma unroll
-          for (int j = 0; j < BF_NK; ++j) {
-            const int g = 2 * (j0 + j) + lh;
-            x[j] = (j < ks && g < B.G) ? load_x(C.xk[0], B.g0 + g, lr) : zero_group3();
-          }
-          for (int d = 0; d < nd; ++d, df += dstep) {
-            const cpx<float> f = C.kin[0] ? pool[tfoff[d0 + d] + C.kp[0]] : cpx<float>{0.f, 0.f};
-            f16v tre = f16_zero(), tim = f16_zero();
-#pragma unroll
-            for (int j = 0; j < BF_NK; ++j) {
-              if (j >= ks) break;
-              const BfGroup a = nxt;
-              if (j + 1 < ks)
-                nxt = load_op(df + (j + 1) * FRAG, lane);
-              else if (d + 1 < nd)
-                nxt = load_op(df + dstep, lane);
-              cstep2(a, x[j], tre, tim);
-            }
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              yre[r] += f.re * tre[r] - f.im * tim[r];
-              yim[r] += f.re * tim[r] + f.im * tre[r];
-            }
-          }
+        // the next piece (the same again after the last)
+        int nj0 = j0 + NK, nbi = bi;
+        if (nj0 >= B.KS) {
+          nj0 = 0;
+          ++nbi;
         }
+        more = nbi < I.nb;
+        if (!more) {
+          nj0 = j0;
+          nbi = bi;
+        }
+        const int nb = rowblk[I.b0 + nbi];
+        const BfBlock N = bb[nb];
+        const uint4* ndf = bfp + (N.off + int64_t(rt) * N.KS + nj0) * FRAG;
+        const int nks = min(NK, N.KS - nj0);
+        auto add = [&](cpx<float> f, const f16v& tre, const f16v& tim) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            yre[r] += f.re * tre[r] - f.im * tim[r];
+            yim[r] += f.re * tim[r] + f.im * tre[r];
+          }
+        };
+        for (int d = 0; d + 1 < nd; ++d) {
+          const cpx<float> f = pool[tfoff[d0 + d] + C.kp[0]];
+          f16v tre = f16_zero(), tim = f16_zero();
+#pragma unroll
+          for (int j = 0; j < NK; ++j) {
+            if (j < ks) cstep2(a[j % NS], x[j], tre, tim);
+            const int jn = (j + NS) % NK;   // of the next term's steps from NK - NS on
+            a[j % NS] = load_op(df + (j + NS < NK ? 0 : dstep) + min(jn, ks - 1) * FRAG, lane);
+          }
+          df += dstep;
+          add(f, tre, tim);
+        }
+        const cpx<float> f = pool[tfoff[d0 + nd - 1] + C.kp[0]];
+        f16v tre = f16_zero(), tim = f16_zero();
+#pragma unroll
+        for (int j = 0; j < NK; ++j) {
+          if (j < ks) cstep2(a[j % NS], x[j], tre, tim);
+          const int jn = (j + NS) % NK;
+          a[j % NS] = load_op(j + NS < NK ? df + min(jn, ks - 1) * FRAG : ndf + min(jn, nks - 1) * FRAG, lane);
+          x[j] = xload(N, nj0 + min(j, nks - 1));
+        }
+        add(f, tre, tim);
+        bi = nbi;
+        j0 = nj0;
+        b = nb;
+        B = N;
+        df = ndf;
       }
       if (C.kin[0]) {
         cpx<float>* yl = Ylev + I.lev * lev_stride;
@@ -936,6 +1016,14 @@ int bf16_setup(gcq_context* ctx) {
   F.bf_items = int(sitems.size());
   F.bf_big = int(big.size());
   F.bf_levels = levels;
+  // pieces of three or four contraction steps, whichever pads the near blocks less:
+  // a step beyond a block's is loaded, not multiplied
+  int64_t pad[2] = {0, 0};
+  for (int b = 0; b < nb; ++b)
+    if (bb[b].G > 0 && !ctx->blocks[b].admissible)
+      for (int i = 0; i < 2; ++i)
+        pad[i] += int64_t(F.brank[b]) * ((bb[b].KS + 2 + i) / (3 + i) * (3 + i) - bb[b].KS);
+  F.bf_nk = pad[0] < pad[1] ? 3 : 4;
   F.bf_bytes = off * FRAG * int64_t(sizeof(uint4));
   F.bf_valid = true;
   return GCQ_OK;
@@ -978,10 +1066,16 @@ static void enqueue_bf_kernels(gcq_context* ctx, hipStream_t st, const uint4* Xg
                      Xg, F.bftbuf.as<uint4>(), Ylev, lev_stride, counter + BF_NX, tmask);
   // near blocks: one frequency tile per wave, two waves a SIMD
   const int nwk = std::min(BF_WAVES, nkt);
-  hipLaunchKernelGGL(bf_near, dim3(ctx->cus * (BF_WAVES / nwk)), dim3(64 * nwk), 0, st, F.d_bfitems.as<BfItem>(),
-                     range + 2 * (BF_NX + 1), F.d_bfrowblk.as<int>(), F.d_bterm.as<int>(), F.d_tfoff.as<int64_t>(),
-                     F.slices.as<cpx<float>>(), F.d_bfblk.as<BfBlock>(), F.bfpool.as<uint4>(), d_colpos, L, ng, Xg,
-                     Ylev, lev_stride, counter + 2 * BF_NX, tmask);
+  auto near = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3(ctx->cus * (BF_WAVES / nwk)), dim3(64 * nwk), 0, st, F.d_bfitems.as<BfItem>(),
+                       range + 2 * (BF_NX + 1), F.d_bfrowblk.as<int>(), F.d_bterm.as<int>(), F.d_tfoff.as<int64_t>(),
+                       F.slices.as<cpx<float>>(), F.d_bfblk.as<BfBlock>(), F.bfpool.as<uint4>(), d_colpos, L, ng, Xg,
+                       Ylev, lev_stride, counter + 2 * BF_NX, tmask);
+  };
+  if (F.bf_nk == 3)
+    near(bf_near<3>);
+  else
+    near(bf_near<4>);
 }
 
 // kernels of one product on stream st (no allocation, no host transfer)
