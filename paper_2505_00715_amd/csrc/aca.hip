@@ -155,7 +155,7 @@ __global__ void __launch_bounds__(NW * 64) recompress_kernel(const PairDesc* __r
                                                              const int* __restrict__ list,
                                                              int* __restrict__ queue) {
   __shared__ cpx<double> mats[GL ? 1 : recompress_mats(MK)];
-  __shared__ RecompSharedT<MK> rs;
+  __shared__ RecompSharedT<MK, NW> rs;
   __shared__ int slot;
   cpx<double>* M = GL ? reinterpret_cast<cpx<double>*>(jws) + int64_t(blockIdx.x) * recompress_mats(MK) : mats;
   int off = 0;

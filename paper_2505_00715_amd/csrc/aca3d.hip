@@ -57,7 +57,7 @@ struct Shared3 {
     cpx<double> mats[BYTES / 16];
   };
   AcaShared<T> aca;
-  RecompShared rs;
+  RecompSharedT<64, NW> rs;
   Term3 term[R3_MAX];
   unsigned char cterm[RES];    // slice of each stacked column
   cpx<T> fk[R3_MAX];           // f_d[k_cur]

@@ -49,22 +49,19 @@ struct AcaShared {
   int nrows;   // rows evaluated by the last approximation
 };
 
-// shared state of one recompression of at most MK terms
-template <int MK>
+// shared state of one recompression of at most MK terms by NW waves
+template <int MK, int NW>
 struct RecompSharedT {
   static constexpr int NP = (MK + 1) / 2;   // index pairs of a Jacobi round
   double sg[MK];
   int keep[MK], order[MK];
   int nkeep, tcut;
-  // one round of the parallel Jacobi ordering, per index pair i: the rotation
-  // {c, Re sigma, Im sigma, -} (the identity when the pair is not rotated), the new
-  // diagonal of the pair's 2 x 2 block, and the pair's indices p | q << 8
-  double4 rot[NP];
-  double2 dia[NP];
-  int pq[NP];
+  // one round of the parallel Jacobi ordering, per index pair: the rotation
+  // {c, Re sigma, Im sigma, -} (the identity when the pair is not rotated); two
+  // rounds where other waves apply it to Q a round later
+  double4 rot[NW > 1 ? 2 : 1][NP];
   double dmax;
 };
-using RecompShared = RecompSharedT<64>;
 
 // working memory of the recompression of k terms (complex doubles)
 __host__ __device__ constexpr int recompress_mats(int k) { return 3 * k * k; }
@@ -344,6 +341,13 @@ __device__ inline int aca_wave(Ent& ent, int m, int n, int cap, int max_rank, do
 __device__ __forceinline__ unsigned quot_mul(int k) { return (unsigned(1 << 18) + k - 1) / k; }
 __device__ __forceinline__ int quot(int e, unsigned mul) { return int((unsigned(e) * mul) >> 18); }
 
+// the wave's own stores to LDS and memory before, its loads after
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+
 // 1 / sqrt(x) to double rounding, x > 0 and finite: the hardware's estimate and
 // two Newton steps
 __device__ __forceinline__ double rsqrt_newton(double x) {
@@ -374,15 +378,18 @@ __device__ __forceinline__ void rotate(double c, cpx<double> s, cpx<double> sc, 
 // result equals the cyclic sweep in that pair order.  A round is three phases:
 // the rotation parameters (a pair whose |b|^2 is below 1e-34 |a d| is not
 // rotated: its b is set to zero, a change below the rounding of a and d), then
-// G^H A G by 2 x 2 blocks (rows of pair i, columns of pair j) and Q G by rows,
-// each thread applying the rotations of its blocks without branches (the
-// identity for pairs not rotated); groups of four waves and more give each
-// update one half of the threads.  A round is a chain of latencies with k/2
-// lanes busy in its first phase, so that phase has no division and no library
-// square root: two reciprocal square roots, by the hardware's start and Newton
-// steps to double rounding.  (With division and square roots, and both updates on
-// every thread: 3D-ACA far kernel on 3648 triangles at 256 frequencies 22.9 ms, now
-// 20.9; on 5120 triangles at 64, 57.5 and 50.6.)
+// G^H A G by 2 x 2 blocks (rows of pair i, columns of pair j, on the upper triangle
+// alone) and Q G by rows.
+// A round is a chain of latencies with k/2 lanes busy in its first phase.  So
+// that phase has no division and no library square root (two reciprocal square
+// roots, by the hardware's start and Newton steps to double rounding).  Groups of
+// one and two waves: the first wave runs it and the update of A with no barrier
+// in between; the second applies the round's rotations to Q during the next
+// round.  Larger groups: half of the waves update A (one wave for it: 22.0 ms
+// against 21.1 below), the other half Q.  3D-ACA far kernel, ms, first with
+// division and every thread in every phase, then now (3648 triangles at 256
+// frequencies / 1280 at 64): one wave a block 67.9 -> 61.8 / 30.7 -> 21.8, two
+// 34.4 -> 32.1 / 19.1 -> 14.9, four 22.9 -> 21.1 / 9.8 -> 9.0.
 // Sweeps stop when the off-diagonal squared Frobenius norm is at most `thr`
 // times the diagonal's.
 // Always inlined: callers pass A and Q either in LDS or in global memory, and
@@ -392,94 +399,116 @@ template <int NW, typename RS>
 __device__ __attribute__((always_inline)) inline void jacobi_grp(cpx<double>* A, cpx<double>* Q,
                                                                  int k, RS& rs, double thr) {
   constexpr int NT = NW * WAVE;
-  constexpr bool HALVES = NW >= 4;             // the two updates on one half of the waves each
-  constexpr int NU = HALVES ? NT / 2 : NT;     // threads of an update
-  const int tid = threadIdx.x;
+  constexpr int AW = NW < 4 ? 1 : NW / 2;   // waves that update A
+  const int tid = threadIdx.x, lane = tid & (WAVE - 1);
+  const int wid = NW == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid / WAVE);
   const unsigned mk = quot_mul(k);
   for (int r = tid; r < k * k; r += NT) Q[r] = {quot(r, mk) * (k + 1) == r ? 1.0 : 0.0, 0.0};
   __syncthreads();
   if (k < 2) return;
   const int ke = (k + 1) & ~1;   // even number of positions (one dummy when k is odd)
-  const int np = ke / 2;
-  // work items of the update phases: (i, j) = (x / np, x % np) for x = tu,
-  // tu + NU, ...; decomposed once and advanced with a carry
-  const int tu = HALVES && tid >= NU ? tid - NU : tid;
-  const bool do_a = !HALVES || tid < NU, do_q = !HALVES || tid >= NU;
-  const int row0 = tu / np, j0 = tu % np, drow = NU / np, dj = NU % np;
+  const int np = ke / 2, nblk = np * (np - 1) / 2;
+  const unsigned mn = quot_mul(np);
+  // pair i of a round, p < q: circle method, position 0 fixed, 1 .. ke - 1 rotate
+  auto pair_of = [&](int i, int round, int& p, int& q) {
+    auto idx = [&](int pos) {
+      int v = pos - 1 + round;   // < 2 (ke - 1)
+      if (v >= ke - 1) v -= ke - 1;
+      return pos == 0 ? 0 : 1 + v;
+    };
+    const int x = idx(i), y = idx(ke - 1 - i);
+    p = min(x, y);
+    q = max(x, y);
+  };
+  // Q G for a round's rotations: row r, columns of pair j, by the threads first,
+  // first + stride, ...
+  auto update_q = [&](int first, int stride, int round, const double4* rot) {
+    for (int x = first; x < k * np; x += stride) {
+      const int r = quot(x, mn), j = x - r * np;
+      int p, q;
+      pair_of(j, round, p, q);
+      if (q >= k) continue;
+      const double4 R = rot[j];
+      cpx<double> u = Q[r * k + p], v = Q[r * k + q];
+      rotate(R.x, {R.y, R.z}, {R.y, -R.z}, u, v);
+      Q[r * k + p] = u;
+      Q[r * k + q] = v;
+    }
+  };
+  int par = 0, last = -1;   // buffer of the next round's rotations; the round before
   for (int sweep = 0; sweep < 40; ++sweep) {
     double off = 0.0, dg = 0.0;
     for (int r = tid; r < k * k; r += NT) {
-      double v = cabs2(A[r]);
-      if (quot(r, mk) * (k + 1) == r) dg += v;
-      else off += v;
+      const double v = cabs2(A[r]);
+      const int row = quot(r, mk), col = r - row * k;
+      if (row == col) dg += v;
+      else if (row < col) off += 2.0 * v;
     }
     grp_sum2<NW>(off, dg);
     if (off <= thr * dg || off == 0.0) break;
     for (int round = 0; round < ke - 1; ++round) {
-      if (tid < np) {
-        // circle method: position 0 fixed, positions 1..ke-1 rotate
-        auto idx = [&](int pos) {
-          if (pos == 0) return 0;
-          int v = pos - 1 + round;   // < 2 (ke - 1)
-          if (v >= ke - 1) v -= ke - 1;
-          return 1 + v;
-        };
-        int p = idx(tid), q = idx(ke - 1 - tid);
-        if (p > q) { int t = p; p = q; q = t; }
-        double c = 1.0, a = 0.0, d = 0.0, tb = 0.0;
-        cpx<double> sg = {0.0, 0.0};
-        if (q < k) {
-          cpx<double> b = A[p * k + q];
-          a = A[p * k + p].re;
-          d = A[q * k + q].re;
-          const double bb2 = cabs2(b);
-          if (bb2 > 1e-300 && bb2 > 1e-34 * fabs(a * d)) {
-            double x = 0.5 * (d - a);
-            // scaled where x^2 would leave the range
-            const bool big = fabs(x) > 1e150;
-            const double sc = big ? 0x1p-500 : 1.0;
-            x *= sc;
-            b = {b.re * sc, b.im * sc};
-            const double b2 = cabs2(b);
-            const double ir = rsqrt_newton(fma(x, x, b2));   // 1 / r
-            const double c2 = fma(0.5 * fabs(x), ir, 0.5);
-            const double ic = rsqrt_newton(c2);
-            c = c2 * ic;
-            const double h = copysign(0.5 * ir * ic, x);
-            sg = {b.re * h, b.im * h};
-            tb = h * ic * b2 * (big ? 0x1p+500 : 1.0);       // tan |b|
-          }
-        }
-        rs.rot[tid] = {c, sg.re, sg.im, 0.0};
-        rs.dia[tid] = {a - tb, d + tb};
-        rs.pq[tid] = p | (q << 8);
-      }
-      __syncthreads();
-      if (do_a) {   // G^H A G: block (rows of pair i, columns of pair j)
-        int i = row0, j = j0;
-        for (int x = tu; x < np * np; x += NU) {
-          const int ci = i, cj = j;
-          i += drow;
-          j += dj;
-          if (j >= np) { j -= np; ++i; }
-          const int pqi = rs.pq[ci], pqj = rs.pq[cj];
-          const int pi = pqi & 255, qi = pqi >> 8, pj = pqj & 255, qj = pqj >> 8;
-          const bool qiv = qi < k, qjv = qj < k;
-          if (ci == cj) {   // the pair's own block becomes diagonal
-            if (qiv) {
-              const double2 dd = rs.dia[ci];
-              A[pi * k + qi] = {0.0, 0.0};
-              A[qi * k + pi] = {0.0, 0.0};
-              A[pi * k + pi] = {dd.x, 0.0};
-              A[qi * k + qi] = {dd.y, 0.0};
+      double4* rot = rs.rot[NW > 1 ? par : 0];
+      if (wid == 0) {
+        if (lane < np) {
+          int p, q;
+          pair_of(lane, round, p, q);
+          double c = 1.0;
+          cpx<double> sg = {0.0, 0.0};
+          if (q < k) {
+            cpx<double> b = A[p * k + q];
+            const double a = A[p * k + p].re, d = A[q * k + q].re;
+            const double bb2 = cabs2(b);
+            double tb = 0.0;
+            if (bb2 > 1e-300 && bb2 > 1e-34 * fabs(a * d)) {
+              double x = 0.5 * (d - a);
+              // scaled where x^2 would leave the range
+              const bool big = fabs(x) > 1e150;
+              const double sc = big ? 0x1p-500 : 1.0;
+              x *= sc;
+              b = {b.re * sc, b.im * sc};
+              const double b2 = cabs2(b);
+              const double ir = rsqrt_newton(fma(x, x, b2));   // 1 / r
+              const double c2 = fma(0.5 * fabs(x), ir, 0.5);
+              const double ic = rsqrt_newton(c2);
+              c = c2 * ic;
+              const double h = copysign(0.5 * ir * ic, x);
+              sg = {b.re * h, b.im * h};
+              tb = h * ic * b2 * (big ? 0x1p+500 : 1.0);       // tan |b|
             }
-            continue;
+            // the pair's own block becomes diagonal
+            A[p * k + q] = {0.0, 0.0};
+            A[p * k + p] = {a - tb, 0.0};
+            A[q * k + q] = {d + tb, 0.0};
           }
-          cpx<double> app = A[pi * k + pj];
-          cpx<double> apq = qjv ? A[pi * k + qj] : cpx<double>{0.0, 0.0};
-          cpx<double> aqp = qiv ? A[qi * k + pj] : cpx<double>{0.0, 0.0};
-          cpx<double> aqq = qiv && qjv ? A[qi * k + qj] : cpx<double>{0.0, 0.0};
-          const double4 Rj = rs.rot[cj], Ri = rs.rot[ci];
+          rot[lane] = {c, sg.re, sg.im, 0.0};
+        }
+        if constexpr (AW == 1) wave_sync();
+      }
+      if constexpr (AW > 1) __syncthreads();
+      if (wid < AW) {
+        // G^H A G: the block of the rows of pair i and the columns of pair j, each
+        // unordered pair of pairs once (j = i + 1 + x / np around the circle)
+        for (int x = tid; x < nblk; x += AW * WAVE) {
+          const int o = quot(x, mn), i = x - o * np;
+          int j = i + 1 + o;
+          if (j >= np) j -= np;
+          int pi, qi, pj, qj;
+          pair_of(i, round, pi, qi);
+          pair_of(j, round, pj, qj);
+          const bool qiv = qi < k, qjv = qj < k;
+          // element (r, c) from the upper triangle
+          auto get = [&](int r, int c, bool in) {
+            cpx<double> v = in ? A[min(r, c) * k + max(r, c)] : cpx<double>{0.0, 0.0};
+            if (r > c) v.im = -v.im;
+            return v;
+          };
+          auto put = [&](int r, int c, bool in, cpx<double> v) {
+            if (r > c) v.im = -v.im;
+            if (in) A[min(r, c) * k + max(r, c)] = v;
+          };
+          cpx<double> app = get(pi, pj, true), apq = get(pi, qj, qjv);
+          cpx<double> aqp = get(qi, pj, qiv), aqq = get(qi, qj, qiv && qjv);
+          const double4 Rj = rot[j], Ri = rot[i];
           {
             const cpx<double> s = {Rj.y, Rj.z}, sc = {Rj.y, -Rj.z};
             rotate(Rj.x, s, sc, app, apq);
@@ -490,32 +519,25 @@ __device__ __attribute__((always_inline)) inline void jacobi_grp(cpx<double>* A,
             rotate(Ri.x, s, sc, app, aqp);
             rotate(Ri.x, s, sc, apq, aqq);
           }
-          A[pi * k + pj] = app;
-          if (qjv) A[pi * k + qj] = apq;
-          if (qiv) A[qi * k + pj] = aqp;
-          if (qiv && qjv) A[qi * k + qj] = aqq;
+          put(pi, pj, true, app);
+          put(pi, qj, qjv, apq);
+          put(qi, pj, qiv, aqp);
+          put(qi, qj, qiv && qjv, aqq);
         }
+        if constexpr (NW == 1) update_q(lane, WAVE, round, rot);
+      } else if (last >= 0) {
+        update_q(tid - AW * WAVE, NT - AW * WAVE, last, rs.rot[NW > 1 ? par ^ 1 : 0]);
       }
-      if (do_q) {   // Q G: row r, columns of pair j
-        int r = row0, j = j0;
-        for (int x = tu; x < k * np; x += NU) {
-          const int cr = r, cj = j;
-          r += drow;
-          j += dj;
-          if (j >= np) { j -= np; ++r; }
-          const int pqj = rs.pq[cj];
-          const int p = pqj & 255, q = pqj >> 8;
-          if (q >= k) continue;
-          const double4 R = rs.rot[cj];
-          cpx<double> u = Q[cr * k + p], v = Q[cr * k + q];
-          rotate(R.x, {R.y, R.z}, {R.y, -R.z}, u, v);
-          Q[cr * k + p] = u;
-          Q[cr * k + q] = v;
-        }
+      if constexpr (NW > 1) {
+        __syncthreads();
+        last = round;
+        par ^= 1;
+      } else {
+        wave_sync();
       }
-      __syncthreads();
     }
   }
+  if (NW > 1 && last >= 0) update_q(tid, NT, last, rs.rot[NW > 1 ? par ^ 1 : 0]);
   __syncthreads();
 }
 
