@@ -445,7 +445,7 @@ def main():
             # full products times the solve's products, at most the solve's time (the
             # solver leaves converged frequency tiles out of its products)
             "per-frequency product (" + ("split-bf16 bf_tfill + bf_rows + bf_near" if PREC_MV == g.C64_SPLIT_BF16 else
-                                        "perfreq_mfma") + "), inside GMRES":
+                                        "perfreq_mm") + "), inside GMRES":
                 min(mv_ms * (iters + 2 * (iters // 50 + 1)), solve.device_ms)}
     dom = max(kern, key=kern.get)
     aca_ops = last["entries"] * 7 * OPS_PER_QPOINT
