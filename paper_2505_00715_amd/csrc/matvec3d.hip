@@ -337,7 +337,7 @@ __global__ void __launch_bounds__(256, 2) perfreq_mm(
   }
 }
 
-// eq. product: a workgroup of four waves per block, up to WS_D terms of it at a
+// eq. product: a workgroup of NT threads per block, up to WS_D terms of it at a
 // time.  Per piece of WS_J columns the frequency sums w1_d (plain columns) and
 // w2_d (conjugate-represented columns, conjugated input) of all those terms form
 // in one pass over X (the fibers staged in LDS, the frequencies dealt to the
@@ -346,20 +346,21 @@ __global__ void __launch_bounds__(256, 2) perfreq_mm(
 // lanes a column, and y = Ubar t, a thread a row.  Bound by the stored slices'
 // bytes, each read once (one wave per block and one term at a time, which read X
 // anew for every term, took 11.4 ms on the 20480-triangle sphere at 64
-// frequencies; now 3.6).  Accumulation into y with atomics.
-constexpr int WS_D = 8, WS_J = 128, WS_K = 64, WS_R = WS_D * 64;
-template <typename T>
-__global__ void __launch_bounds__(256) wsum_kernel(
+// frequencies; now 3.6 with four waves and eight terms).  Accumulation into y with
+// atomics.
+template <typename T, int NT, int WS_D, int WS_J, int WS_K>
+__global__ void __launch_bounds__(NT) wsum_kernel(
     const int* __restrict__ blk, const int* __restrict__ order, int nblocks, const int* __restrict__ bterm,
     const int* __restrict__ trank, const int64_t* __restrict__ toff,
     const int64_t* __restrict__ tvoff, const int64_t* __restrict__ tfoff,
     const cpx<T>* __restrict__ pool, const int* __restrict__ colpos,
     const int* __restrict__ conjf, int L, int n,
     const cpx<T>* __restrict__ X, cpx<T>* __restrict__ ybuf) {
+  constexpr int WS_R = WS_D * 64;
   __shared__ cpx<T> ws[2][WS_D][WS_J];
   __shared__ cpx<T> fs[WS_D][WS_K];
   __shared__ cpx<T> ts[2][WS_R];
-  __shared__ cpx<T> red[256];
+  __shared__ cpx<T> red[NT];
   __shared__ unsigned char cterm[WS_R];
   __shared__ unsigned char cj[WS_K];
   const int tid = threadIdx.x;
@@ -367,8 +368,8 @@ __global__ void __launch_bounds__(256) wsum_kernel(
     const int b = order[ob];   // blocks with terms, most work first
     const int rb = blk[5 * b], m = blk[5 * b + 1] - rb, cb = blk[5 * b + 2], nn = blk[5 * b + 3] - cb;
     const bool far = trank[bterm[b]] >= 0;
-    const int jt = nn <= 64 ? 64 : WS_J, kg = tid / jt, nkg = 256 / jt, jl = tid % jt;
-    const int it = m <= 64 ? 64 : m <= 128 ? 128 : 256, ig = tid / it, nig = 256 / it;
+    const int jt = nn <= 64 ? 64 : WS_J, kg = tid / jt, nkg = NT / jt, jl = tid % jt;
+    const int it = min(NT, m <= 64 ? 64 : m <= 128 ? 128 : 256), ig = tid / it, nig = NT / it;
     for (int d0 = bterm[b]; d0 < bterm[b + 1]; d0 += WS_D) {
       const int nd = min(WS_D, bterm[b + 1] - d0);
       int R = 0;
@@ -376,7 +377,7 @@ __global__ void __launch_bounds__(256) wsum_kernel(
       if (far)
         for (int d = 0; d < nd; ++d) {
           const int r = trank[d0 + d];
-          for (int c = tid; c < r; c += 256) cterm[R + c] = (unsigned char)d;
+          for (int c = tid; c < r; c += NT) cterm[R + c] = (unsigned char)d;
           R += r;
         }
       for (int j0 = 0; j0 < nn; j0 += WS_J) {
@@ -387,7 +388,7 @@ __global__ void __launch_bounds__(256) wsum_kernel(
         for (int k0 = 0; k0 < L; k0 += WS_K) {
           const int kn = min(WS_K, L - k0);
           __syncthreads();
-          for (int e = tid; e < WS_D * WS_K; e += 256) {
+          for (int e = tid; e < WS_D * WS_K; e += NT) {
             const int d = e / WS_K, k = e % WS_K;
             fs[d][k] = (d < nd && k < kn) ? pool[tfoff[d0 + d] + colpos[k0 + k]] : cpx<T>{T(0), T(0)};
           }
@@ -427,7 +428,7 @@ __global__ void __launch_bounds__(256) wsum_kernel(
           // t[c] over this piece of columns, 16 lanes a column
           const cpx<T>* V = pool + tvoff[d0] + j0;
           const int q = tid & 15;
-          for (int c = tid >> 4; c < R; c += 16) {
+          for (int c = tid >> 4; c < R; c += NT / 16) {
             const int d = cterm[c];
             const cpx<T>* Vc = V + int64_t(c) * nn;
             T r1 = 0, i1 = 0, r2 = 0, i2 = 0;
@@ -640,11 +641,23 @@ static int compressed_impl(gcq_context* ctx, int mode, int precision, const void
       hipLaunchKernelGGL((perm_in3<float, T>), dim3(g), dim3(256), 0, st, (const cpx<float>*)X, Xp,
                          perm, ctx->scratchD.as<int>(), n, L);
     hipLaunchKernelGGL(zero3<T>, dim3(64), dim3(256), 0, st, Yp, int64_t(n));
-    hipLaunchKernelGGL(wsum_kernel<T>, dim3(wgrid), dim3(256), 0, st, ctx->d_blk.as<int>(),
-                       F.d_mvorder.as<int>(), nmv,
-                       F.d_bterm.as<int>(), F.d_trank.as<int>(), F.d_toff.as<int64_t>(),
-                       F.d_tvoff.as<int64_t>(), F.d_tfoff.as<int64_t>(), F.slices.as<cpx<T>>(),
-                       d_colpos, d_conj, L, n, Xp, Yp);
+    auto wsum = [&](auto kern, int nt) {
+      hipLaunchKernelGGL(kern, dim3(wgrid), dim3(nt), 0, st, ctx->d_blk.as<int>(), F.d_mvorder.as<int>(), nmv,
+                         F.d_bterm.as<int>(), F.d_trank.as<int>(), F.d_toff.as<int64_t>(), F.d_tvoff.as<int64_t>(),
+                         F.d_tfoff.as<int64_t>(), F.slices.as<cpx<T>>(), d_colpos, d_conj, L, n, Xp, Yp);
+    };
+    // Many narrow blocks at few frequencies: a wave and two terms at a time, where
+    // four waves and their barriers find too little work in a block.  The line, by
+    // the mean side of the near blocks (a leaf's width) times the frequencies and by
+    // the blocks, in us, one wave / four waves: 18000 triangles in leaves of 18 at 6
+    // frequencies 882 / 1497, 8133 in leaves of 32 at 8 1352 / 1643, 10972 in leaves
+    // of 21 at 10 1710 / 1735; 6661 in leaves of 26 at 14 1445 / 1011, 720 (few
+    // blocks) in leaves of 22 at 6 86 / 73.
+    const double side = std::sqrt(double(ctx->near_total) / std::max<size_t>(ctx->near_ids.size(), 1));
+    if (nmv >= 4 * ctx->cus && side * L <= 260.0)
+      wsum(wsum_kernel<T, 64, 2, 64, 32>, 64);
+    else
+      wsum(wsum_kernel<T, 256, 8, 128, 64>, 256);
     if (precision == GCQ_C128)
       hipLaunchKernelGGL((perm_out3<T, double>), dim3(64), dim3(256), 0, st, Yp, (cpx<double>*)Y,
                          perm, ctx->scratchD.as<int>(), n, 1);
