@@ -22,8 +22,9 @@
 // Y_I += sum_d f_d o (D_d X_J).  Work items are rows of one row cluster with all
 // its far (or all its near) blocks; a workgroup's waves own the frequency
 // columns, accumulate the item's rows in registers and store them once into
-// the level buffer of the cluster's depth (near blocks: a level after the
-// deepest); a last pass sums the levels of each row into Y.  No atomics.
+// the level buffer of the cluster's depth (near blocks, and the further pieces
+// of a block list that was cut: levels of their own after the deepest, one per
+// depth and piece); a last pass sums the levels of each row into Y.  No atomics.
 #include <algorithm>
 #include <cstring>
 #include <numeric>
